@@ -26,7 +26,8 @@
 // k-tiles of the same pipeline.  The projection X_x Vt2^T runs on the fp16
 // MFMA with Vt2 the fp16 hi/lo split of 256 V (the low parts of entries near
 // 1/sqrt(n) then stay normal); the combine multiplies by 1/256 (exact).
-// fp32 inputs: Vt (rp x n), P = X Vt^T and B_b in fp32, fp32 FMA throughout.
+// fp32 inputs: Vt (rp x n), P = X Vt^T and B_b in fp32, the products on the fp32 MFMA
+// (zo_gemm_f32.hip).
 //
 // The main GEMM (k_gemm_main) is described where it is defined.  The
 // register-staged GEMM (k_gemm_bf16: the projection of wide factors and the
@@ -120,21 +121,12 @@ __device__ __forceinline__ void add4(const char* base, size_t idx, float& v0, fl
   v0 += r[0]; v1 += r[1]; v2 += r[2]; v3 += r[3];
 }
 
-// silu(x) = x / (1 + e^-x) from the hardware exponential and reciprocal (about 1 ulp each,
-// so a few fp32 ulps in all, far below the output's 16-bit rounding): the IEEE expf and
-// division cost ~28 VALU instructions per element, and the epilogue of a 256 x 256 tile
-// applies it to 256 values per lane while the matrix cores idle.  e^-x overflows to +inf
-// for x < -88, and the reciprocal then gives 0: silu(x) -> -0, its limit.
-__device__ __forceinline__ float silu(float x) {
-  return x * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(x * -1.4426950408889634f));
-}
-
 // v0..v3 multiplied by silu of the four OUT-typed values at element idx.. (fp32).
 template <int OUT>
 __device__ __forceinline__ void mul4_silu(const char* base, size_t idx, float& v0, float& v1, float& v2,
                                           float& v3) {
   const f32x4 r = load4<OUT>(base, idx);
-  v0 *= silu(r[0]); v1 *= silu(r[1]); v2 *= silu(r[2]); v3 *= silu(r[3]);
+  v0 *= zo_silu(r[0]); v1 *= zo_silu(r[1]); v2 *= zo_silu(r[2]); v3 *= zo_silu(r[3]);
 }
 
 // The fused epilogue on four fp32 accumulator values, then the store: ReLU, the residual R
@@ -405,95 +397,6 @@ __global__ __launch_bounds__(WM* WN * 64) void k_gemm_bf16(GemmArgs a) {
         finish4_rt(Yb, Rb, (size_t)tok * a.ldy + col, a.out_dtype, a.epi, acc[i][j][q4 * 4 + 0],
                    acc[i][j][q4 * 4 + 1], acc[i][j][q4 * 4 + 2], acc[i][j][q4 * 4 + 3]);
       }
-    }
-  }
-}
-
-// fp32 path: plain 64x64 tile GEMM, fp32 FMA, with the same correction term.
-struct F32Args {
-  const float* A;  // rows_a x K
-  const float* B;  // per block rows_b x K
-  long long b_block_stride;
-  int rows_a, rows_b, K;
-  const float* ca;  // per block rows_a x rc
-  long long ca_block_stride;
-  const float* cb;  // per block rows_b x rc
-  long long cb_block_stride;
-  int rc;
-  float* Y;
-  long long y_block_stride;
-  int ldy;
-  int epi;                    // zo_epilogue
-  const float* R;             // ZO_EPI_RESIDUAL: added to Y (same layout)
-  long long r_block_stride;
-  const float* base;          // nullptr, or a rows_b x ldy matrix added before the epilogue
-};
-
-__global__ __launch_bounds__(256) void k_gemm_f32(F32Args a) {
-  __shared__ float sb[16][68];
-  __shared__ float sa[16][68];
-  const int blk = blockIdx.z;
-  const int t0 = blockIdx.y * 64;
-  const int c0 = blockIdx.x * 64;
-  const float* __restrict__ B = a.B + (long long)blk * a.b_block_stride;
-  const float* __restrict__ A = a.A;
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  float acc[4][4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
-  for (int k0 = 0; k0 < a.K; k0 += 16) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      const int e = threadIdx.x + 256 * i;
-      const int row = e >> 4, kk = e & 15;
-      const int k = k0 + kk;
-      sb[kk][row] = (t0 + row < a.rows_b && k < a.K) ? B[(size_t)(t0 + row) * a.K + k] : 0.f;
-      sa[kk][row] = (c0 + row < a.rows_a && k < a.K) ? A[(size_t)(c0 + row) * a.K + k] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < 16; ++kk)
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = fmaf(sb[kk][ty * 4 + i], sa[kk][tx * 4 + j], acc[i][j]);
-    __syncthreads();
-  }
-  if (a.rc > 0) {
-    const float* __restrict__ C = a.ca + (long long)blk * a.ca_block_stride;
-    const float* __restrict__ D = a.cb + (long long)blk * a.cb_block_stride;
-    for (int c = 0; c < a.rc; ++c) {
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const int tok = t0 + ty * 4 + i;
-        const float p = tok < a.rows_b ? D[(size_t)tok * a.rc + c] : 0.f;
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int col = c0 + tx * 4 + j;
-          const float q = col < a.rows_a ? C[(size_t)col * a.rc + c] : 0.f;
-          acc[i][j] = fmaf(p, q, acc[i][j]);
-        }
-      }
-    }
-  }
-  float* Y = a.Y + (long long)blk * a.y_block_stride;
-  const float* R = a.R + (long long)blk * a.r_block_stride;
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int tok = t0 + ty * 4 + i;
-    if (tok >= a.rows_b) continue;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int col = c0 + tx * 4 + j;
-      if (col >= a.rows_a) continue;
-      float v = acc[i][j];
-      if (a.base) v += a.base[(size_t)tok * a.ldy + col];
-      if (a.epi == ZO_EPI_RELU) v = fmaxf(v, 0.f);
-      if (a.epi == ZO_EPI_RESIDUAL) v += R[(size_t)tok * a.ldy + col];
-      if (a.epi == ZO_EPI_SILU_MUL) v *= silu(R[(size_t)tok * a.ldy + col]);
-      Y[(size_t)tok * a.ldy + col] = v;
     }
   }
 }
@@ -1181,7 +1084,7 @@ __global__ __launch_bounds__(256, 1) void k_gemm_main(GemmArgs a) {
             if constexpr (EPI == ZO_EPI_RELU) v[e] = fmaxf(v[e], 0.f);
             else if constexpr (EPI == ZO_EPI_RESIDUAL || EPI == EPI_BASE) v[e] += rv[e];
             else if constexpr (EPI == EPI_BASE_RELU) v[e] = fmaxf(v[e] + rv[e], 0.f);
-            else v[e] *= silu(rv[e]);
+            else v[e] *= zo_silu(rv[e]);
           }
         }
         store8<OUT>(Yb, idx, v);
@@ -1716,13 +1619,11 @@ int zo_plinear_project(const PlinearPlan& p, const void* X, void* ws, hipStream_
   g.rows_a = p.rp;
   g.rows_b = p.T;
   g.K = p.n;
-  g.rc = 0;
+  g.nblk = p.nx;
   g.Y = (float*)pp;
   g.y_block_stride = (long long)p.T * p.rp;
   g.ldy = p.rp;
-  dim3 grid((p.rp + 63) / 64, (p.T + 63) / 64, p.nx);
-  hipLaunchKernelGGL(k_gemm_f32, grid, dim3(256), 0, stream, g);
-  return zo_hip_status(hipGetLastError(), "k_gemm_f32 (projection)");
+  return zo_gemm_f32_narrow(g, stream);
 }
 
 int zo_gemm_plain(int T, int m, int n, int nblk, int dtype, const void* X, long long x_block_stride,
@@ -1849,28 +1750,31 @@ int zo_plinear_apply(const PlinearPlan& p, const void* X, const void* W, void* Y
   h.cb = (const float*)pp;
   h.cb_block_stride = p.nx == 1 ? 0 : (long long)p.T * p.rp;
   h.rc = p.rp;
+  h.nblk = p.nblk;
   h.Y = (float*)Y;
   h.y_block_stride = (long long)p.T * p.m;
   h.ldy = p.m;
   h.epi = epi;
   h.R = (const float*)R;
   h.r_block_stride = r_block_stride;
-  if (p.fan) {
-    // Shared X: X W^T once into the base, then each block's rank-r term added to it.
-    F32Args b = h;
-    b.rc = 0;
-    b.Y = (float*)w.base;
-    b.y_block_stride = 0;
-    b.epi = ZO_EPI_NONE;
-    b.R = nullptr;
-    b.r_block_stride = 0;
-    hipLaunchKernelGGL(k_gemm_f32, dim3((p.m + 63) / 64, (p.T + 63) / 64, 1), dim3(256), 0, stream, b);
-    int st = zo_hip_status(hipGetLastError(), "k_gemm_f32 (shared X)");
-    if (st != ZO_OK) return st;
-    h.K = 0;
-    h.base = (const float*)w.base;
+  if (!p.fan) return zo_gemm_f32(h, stream);
+  // Shared X: X W^T once, then each block's rank-r term added to it; in one launch where the
+  // product has too few tiles to fill the chip, else through the base in the workspace.
+  F32Args b = h;
+  b.rc = 0;
+  b.nblk = 1;
+  b.Y = (float*)w.base;
+  b.y_block_stride = 0;
+  b.epi = ZO_EPI_NONE;
+  b.R = nullptr;
+  b.r_block_stride = 0;
+  if (zo_gemm_f32_fans(b)) {
+    h.fan = p.nblk;
+    return zo_gemm_f32_fan(h, stream);
   }
-  dim3 grid((p.m + 63) / 64, (p.T + 63) / 64, p.nblk);
-  hipLaunchKernelGGL(k_gemm_f32, grid, dim3(256), 0, stream, h);
-  return zo_hip_status(hipGetLastError(), "k_gemm_f32");
+  const int st = zo_gemm_f32(b, stream);
+  if (st != ZO_OK) return st;
+  h.K = 0;
+  h.base = (const float*)w.base;
+  return zo_gemm_f32(h, stream);
 }

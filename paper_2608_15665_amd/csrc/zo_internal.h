@@ -89,6 +89,15 @@ __device__ __forceinline__ void put_split(void* Vt, long long idx, long long lo_
   }
 }
 
+// silu(x) = x / (1 + e^-x) from the hardware exponential and reciprocal (about 1 ulp each,
+// so a few fp32 ulps in all, far below the output's 16-bit rounding): the IEEE expf and
+// division cost ~28 VALU instructions per element, and the epilogue of a 256 x 256 tile
+// applies it to 256 values per lane while the matrix cores idle.  e^-x overflows to +inf
+// for x < -88, and the reciprocal then gives 0: silu(x) -> -0, its limit.
+__device__ __forceinline__ float zo_silu(float x) {
+  return x * __builtin_amdgcn_rcpf(1.f + __builtin_amdgcn_exp2f(x * -1.4426950408889634f));
+}
+
 // ---------------------------------------------------------------- launchers
 // Perturbed linear (zo_gemm.hip).
 struct PlinearPlan {
@@ -144,6 +153,34 @@ int zo_plinear_prepare_group(const PlinearPlan* plans, int count, const int* blk
                              const int8_t* blk_sign, float eps, const void* X, const float* const* U,
                              const float* const* V, const float* const* Z, void* const* ws, void* gws,
                              hipStream_t stream);
+// fp32 GEMM (zo_gemm_f32.hip): Y_b = B_b A^T + D_b C_b^T (D: cb, C: ca), plus base, epilogue.
+struct F32Args {
+  const float* A;  // rows_a x K, shared by all blocks
+  const float* B;  // per block rows_b x K
+  long long b_block_stride;
+  int rows_a, rows_b, K, nblk;
+  const float* ca;  // per block rows_a x rc
+  long long ca_block_stride;
+  const float* cb;  // per block rows_b x rc
+  long long cb_block_stride;
+  int rc;           // a multiple of 16; 0 = no rank-r term
+  float* Y;         // per block rows_b x ldy
+  long long y_block_stride;
+  int ldy;
+  int epi;                   // zo_epilogue
+  const float* R;            // ZO_EPI_RESIDUAL / ZO_EPI_SILU_MUL: layout of Y
+  long long r_block_stride;
+  const float* base;         // nullptr, or a rows_b x ldy matrix added before the epilogue
+  int fan;                   // zo_gemm_f32_fan: blocks formed from one B A^T
+  int tiles_a, tiles_b, total_tiles;  // set by the launcher
+};
+int zo_gemm_f32(const F32Args& a, hipStream_t stream);
+// The same for an A of few rows (the projection X V: rows_a = rp).
+int zo_gemm_f32_narrow(const F32Args& a, hipStream_t stream);
+// Whether the blocks of one shared B (nblk = 1 in a) are better formed in one launch, and that
+// launch: `fan` blocks, each B A^T plus its own rank-r term.
+bool zo_gemm_f32_fans(const F32Args& a);
+int zo_gemm_f32_fan(const F32Args& a, hipStream_t stream);
 // Decoder-layer pieces (zo_decoder.hip).
 int zo_layernorm_launch(long long rows, int d, int dtype, const void* X, const float* gamma,
                         const float* beta, float eps_ln, void* Y, hipStream_t stream, bool rms = false);
