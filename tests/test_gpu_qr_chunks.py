@@ -1,0 +1,63 @@
+"""The refresh's short and long row chunks, and its two row kernels (r <= 64 and r <= 128).
+
+A panel's sums are the same tree whatever the chunk length, so its Q, diag(R) and info are the same
+bits alone (short chunks, partials in its output), in place (long chunks: the output lies over
+Omega) and among enough panels to make the call take long chunks; and against a float64 Householder
+QR with the sign fix at the refresh's bar (1e-5 elementwise; the factor is exact to fp32 rounding,
+so 2e-7 normwise holds with room).  Rows sit on the edges of the units (128 and 256 rows), the short
+chunks (512 and 256) and the long ones (2048)."""
+import numpy as np
+import pytest
+import torch
+
+import paper_2608_15665_amd as zo
+from _common import dev_f32, normwise
+
+pytestmark = pytest.mark.gpu
+
+ROWS = {
+    1: [1, 7, 512, 513, 2049],        # an output smaller than its partials: long chunks
+    15: [15, 127, 128, 129, 4097],
+    17: [511, 513, 2047, 6000],
+    48: [48, 640, 2048],
+    64: [64, 2050, 5120, 8191],
+    65: [65, 255, 257, 2049],
+    100: [128, 512, 4100],
+    128: [128, 129, 2047, 2048, 8193],
+}
+
+
+def _ref(om):
+    Q, R = np.linalg.qr(om.astype(np.float64))
+    s = np.sign(np.diag(R))
+    return Q * s, np.abs(np.diag(R))
+
+
+@pytest.mark.parametrize("r", sorted(ROWS))
+def test_chunks_agree_bitwise_and_with_householder(r):
+    rng = np.random.default_rng(r)
+    host = [rng.standard_normal((rows, r)).astype(np.float32) for rows in ROWS[r]]
+    oms = [dev_f32(h) for h in host]
+
+    def run(om, out, many=False):
+        n = len(om)
+        rd = [torch.empty(r, device="cuda") for _ in range(n)]
+        info = torch.full((n,), -1, dtype=torch.int32, device="cuda")
+        zo.subspace_refresh(om, r, out=out, r_diag=rd, info=info)
+        return [o.cpu().numpy() for o in out], [d.cpu().numpy() for d in rd], info.cpu().numpy()
+
+    alone, rda, infa = run(oms, [torch.full_like(o, float("nan")) for o in oms])
+    place = [o.clone() for o in oms]
+    inpl, rdi, infi = run(place, place)
+    filler = dev_f32(rng.standard_normal((max(r, 32), r)))
+    crowd = oms + [filler] * 70  # more panels than a call with short chunks holds
+    many, rdm, _ = run(crowd, [torch.empty_like(o) for o in crowd])
+    for p, h in enumerate(host):
+        for q, d in ((inpl, rdi), (many, rdm)):
+            np.testing.assert_array_equal(alone[p].view(np.uint32), q[p].view(np.uint32), err_msg=str(h.shape))
+            np.testing.assert_array_equal(rda[p].view(np.uint32), d[p].view(np.uint32))
+        if h.shape[0] >= 2 * r:
+            Q, R = _ref(h)
+            assert np.abs(alone[p] - Q).max() <= 1e-5 and normwise(alone[p], Q) <= 2e-7, h.shape
+            assert normwise(rda[p], R) <= 2e-7
+    assert not infa.any() and not infi.any()
