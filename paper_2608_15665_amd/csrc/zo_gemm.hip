@@ -40,17 +40,14 @@
 // tiles in flight on an XCD share their W and X panels in that XCD's L2.
 #include "zo_internal.h"
 
+#include <algorithm>
 #include <type_traits>
 
 namespace {
 
 constexpr int BK = 64;  // bf16 elements per K tile = 128 bytes per LDS row
 
-// Internal epilogues of the shared-X fan-out (beyond zo_epilogue's values): R is an fp32 T x m
-// base X W^T shared by every block, added to the block's rank-r term before the rounding.
-constexpr int EPI_BASE = 16;       // Y_b = base + result
-constexpr int EPI_BASE_RELU = 17;  // Y_b = max(base + result, 0)
-// The prepare's projection of a stack of 16-bit factors (A = the stacked [V_hi; V_lo] rows, 2 rp
+// Internal epilogues beyond zo_epilogue's values.  The prepare's projection of a stack of 16-bit factors (A = the stacked [V_hi; V_lo] rows, 2 rp
 // per factor, rp = 32 or 64): P = (hi part + lo part) * unscale of every factor, written to the
 // factor's own buffer as [P_hi | P_hi | P_lo] (bf16, 3 rp per token); Y is not used.
 constexpr int EPI_PROJ32 = 18;
@@ -77,7 +74,6 @@ struct GemmArgs {
   const void* R;               // ZO_EPI_RESIDUAL / SILU_MUL: same type and layout as Y (ldy)
   long long r_block_stride;    // elements; 0 = one R shared by all blocks
   int tiles_a, tiles_b, total_tiles;
-  int blk_inner;               // k_gemm_main: 1 = the blocks of one output tile run consecutively
   // EPI_PROJ32 / EPI_PROJ64: factor f's output (nblk x rows_b tokens x 3 rp), the number of
   // factors, and the scale of the combined projection (1, or 1/256 for fp16 inputs).
   bf16_t* pc[ZO_MAX_GROUP];
@@ -670,22 +666,19 @@ __global__ __launch_bounds__(256, 1) void k_gemm_main(GemmArgs a) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wm = wave & 1, wn = wave >> 1;
 
-  // XCD-aware tile order (each XCD a contiguous range), grouped 8 token tiles deep.  With
-  // blk_inner the block index runs fastest (the shared-X fan-out: the blocks of one tile read
-  // the same base tile, which then comes from the XCD's L2).
+  // XCD-aware tile order (each XCD a contiguous range), grouped 8 token tiles deep.
   const int w = blockIdx.x;
   const int nt = a.total_tiles;
   const int xcd = w & 7, widx = w >> 3;
-  const int lt0 = xcd * (nt >> 3) + min(xcd, nt & 7) + widx;
-  const int lt = a.blk_inner ? lt0 / a.nblk : lt0;
-  const int nbt = a.blk_inner ? a.tiles_b : a.nblk * a.tiles_b;  // (block, token tile) pairs in the raster
+  const int lt = xcd * (nt >> 3) + min(xcd, nt & 7) + widx;
+  const int nbt = a.nblk * a.tiles_b;  // (block, token tile) pairs in the raster
   constexpr int GROUP = 8;
   const int per_group = GROUP * a.tiles_a, grp = lt / per_group, first = grp * GROUP;
   const int gsize = min(GROUP, nbt - first), rem = lt - grp * per_group;
   const int bt = first + rem % gsize, at = rem / gsize;
   // The decode is uniform but its divisions run on the VALU: pin the results to scalar
   // registers, so the buffer descriptors built from them are scalar too.
-  const int blk = __builtin_amdgcn_readfirstlane(a.blk_inner ? lt0 % a.nblk : bt / a.tiles_b);
+  const int blk = __builtin_amdgcn_readfirstlane(bt / a.tiles_b);
   const int t0 = __builtin_amdgcn_readfirstlane((bt % a.tiles_b) * 256);
   const int m0 = __builtin_amdgcn_readfirstlane(at * 256);
 
@@ -1018,23 +1011,18 @@ __global__ __launch_bounds__(256, 1) void k_gemm_main(GemmArgs a) {
     const int col = m0 + (wave * 8 + lc8) * 8;
     // R of the half's read-back passes is requested before its staging writes, so that its
     // latency overlaps them (one load chain per half instead of one per few passes).
-    constexpr bool HAS_R = EPI == ZO_EPI_RESIDUAL || EPI == ZO_EPI_SILU_MUL || EPI == EPI_BASE ||
-                           EPI == EPI_BASE_RELU;
-    constexpr bool R32 = EPI == EPI_BASE || EPI == EPI_BASE_RELU;  // the fp32 base
+    constexpr bool HAS_R = EPI == ZO_EPI_RESIDUAL || EPI == ZO_EPI_SILU_MUL;
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
       if (h) __syncthreads();  // the first half's read-back is done
-      u32x4 rpre[HAS_R ? 16 : 1][R32 || OUT == ZO_F32 ? 2 : 1];
+      u32x4 rpre[HAS_R ? 16 : 1][OUT == ZO_F32 ? 2 : 1];
       if constexpr (HAS_R) {
 #pragma unroll
         for (int it = 0; it < 16; ++it) {
           const int sr = it * 8 + lr8;
           const int tok = t0 + (sr >> 6) * 128 + h * 64 + (sr & 63);
           const size_t idx = (size_t)min(tok, a.rows_b - 1) * a.ldy + min(col, a.rows_a - 8);
-          if constexpr (R32) {  // 32-byte aligned rows
-            rpre[it][0] = *(const u32x4*)(Rb + idx * 4);
-            rpre[it][1] = *(const u32x4*)(Rb + idx * 4 + 16);
-          } else if constexpr (OUT == ZO_F32) {  // an fp32 R need only be 4-byte aligned
+          if constexpr (OUT == ZO_F32) {  // an fp32 R need only be 4-byte aligned
             float r8[8];
             load8<ZO_F32>(Rb, idx, r8);
             rpre[it][0] = __builtin_bit_cast(u32x4, (f32x4){r8[0], r8[1], r8[2], r8[3]});
@@ -1061,7 +1049,7 @@ __global__ __launch_bounds__(256, 1) void k_gemm_main(GemmArgs a) {
         if constexpr (EPI != ZO_EPI_NONE) {
           float rv[8];
           if constexpr (HAS_R) {
-            if constexpr (R32 || OUT == ZO_F32) {
+            if constexpr (OUT == ZO_F32) {
               const f32x4 r0 = __builtin_bit_cast(f32x4, rpre[it][0]), r1 = __builtin_bit_cast(f32x4, rpre[it][1]);
               rv[0] = r0[0]; rv[1] = r0[1]; rv[2] = r0[2]; rv[3] = r0[3];
               rv[4] = r1[0]; rv[5] = r1[1]; rv[6] = r1[2]; rv[7] = r1[3];
@@ -1082,8 +1070,7 @@ __global__ __launch_bounds__(256, 1) void k_gemm_main(GemmArgs a) {
 #pragma unroll
           for (int e = 0; e < 8; ++e) {
             if constexpr (EPI == ZO_EPI_RELU) v[e] = fmaxf(v[e], 0.f);
-            else if constexpr (EPI == ZO_EPI_RESIDUAL || EPI == EPI_BASE) v[e] += rv[e];
-            else if constexpr (EPI == EPI_BASE_RELU) v[e] = fmaxf(v[e] + rv[e], 0.f);
+            else if constexpr (EPI == ZO_EPI_RESIDUAL) v[e] += rv[e];
             else v[e] *= zo_silu(rv[e]);
           }
         }
@@ -1266,6 +1253,215 @@ __global__ __launch_bounds__(256, 1) void k_proj(ProjArgs a) {
   }
 }
 
+// Fan-out of a shared X: Y_b = base + P B_b^T for every block b, with base = X W^T (fp32, T x m,
+// from the main GEMM) and the prepared rank-r operands P (one for all blocks) and B_b.
+//
+// What it cannot do without is writing the outputs, so it is built around them: a workgroup holds
+// a 128 x 128 tile of the base in registers (each wave 64 x 64) with its P fragments, and walks the
+// blocks; per block only B_b's 128 rows ([B_hi | B_lo], 4 RP bytes each; they come from L2) and the
+// outputs move.  The terms are added in the segment's order (P_hi B_hi, P_hi B_lo, P_lo B_hi, k
+// ascending) from zero, then the base: the bits are those of a rank-only GEMM with the base added
+// at the end.
+//
+// A wave's vector memory operations complete in order, so a load waits for the stores issued before
+// it.  B_b therefore comes to LDS by direct loads two blocks ahead, issued between a block's MFMAs
+// and its stores, and the wait before a block allows everything issued since its loads: the
+// stores of two blocks stay in flight.  (Loads one block ahead, behind the stores of the block
+// before: 545 us below.)
+//
+// P is the MFMA's A operand and B_b's rows its B operand, row 4 (l % 16) + j of the wave's 64
+// being column l % 16 of tile j: a lane ends with 4 adjacent output columns of a token, and a store
+// instruction covers 128 contiguous bytes (256 for fp32) of 4 tokens, whole cache lines.  The 16
+// rows a fragment read touches are 4 apart; the chunk swizzle fan_swz takes the row bits that vary,
+// so those reads are conflict free.
+//
+// Every global access of the loop is a buffer instruction over exactly the tile's rows, columns
+// past m given an offset out of range, so the count of stores per block is fixed.
+//
+// T = 8192, m = n = 5120, r = 64, 16 blocks, bf16: 882 -> 380 us (1.34 GB written, 3.5 TB/s; 410
+// without the non-temporal hint, 311 without the loads of B_b), against a rank-only launch of the
+// main GEMM that read the base again for every block.
+struct FanArgs {
+  const float* base;   // T x m
+  const bf16_t* pp;    // T x 3 RP: [P_hi | P_hi | P_lo]
+  const bf16_t* bp;    // per block m x 3 RP: [B_hi | B_lo | B_hi]
+  void* Y;             // per block T x m
+  int T, m, nblk, relu;
+  int tiles_m, tiles_t, total_tiles, splits;  // splits: workgroups that share a tile's blocks
+};
+
+template <int RPK>
+__device__ __forceinline__ int fan_swz(int row) {
+  return (row >> 2) & (RPK % 2 ? 7 : 15);
+}
+
+// s_waitcnt vmcnt(N), for the counts k_fan needs.
+template <int N>
+__device__ __forceinline__ void wait_vm() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+template <int RPK, int OUT>
+__global__ __launch_bounds__(256, RPK <= 2 ? 2 : 1) void k_fan(FanArgs a) {
+  constexpr int RP = 32 * RPK, CH = RP / 4;       // 16-byte chunks of a [B_hi | B_lo] row
+  constexpr int ROWB = CH * 16, BUF = 128 * ROWB;  // bytes per staged row, per buffer
+  constexpr int ND = 128 * CH / 256;               // DMA loads per thread per block
+  constexpr int OSZ = OUT == ZO_F32 ? 4 : 2;
+  constexpr int NS = 16;                           // stores per lane per block
+  constexpr int NT = 2;                            // cache policy of the stores: non-temporal
+  __shared__ __attribute__((aligned(1024))) char lds[2 * BUF];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wm = wave & 1, wt = wave >> 1;
+  // Each XCD a contiguous range of tiles, 8 token tiles deep per column sweep: the workgroups an
+  // XCD runs at once share few B_b row panels.
+  const int w = blockIdx.x, nt = a.total_tiles;
+  const int xcd = w & 7, widx = w >> 3;
+  const int lt = xcd * (nt >> 3) + min(xcd, nt & 7) + widx;
+  constexpr int GROUP = 8;
+  const int per_group = GROUP * a.tiles_m, grp = lt / per_group, first = grp * GROUP;
+  const int gsize = min(GROUP, a.tiles_t - first), rem = lt - grp * per_group;
+  const int t0 = __builtin_amdgcn_readfirstlane((first + rem % gsize) * 128);
+  const int m0 = __builtin_amdgcn_readfirstlane((rem / gsize) * 128);
+  const int fr = lane & 15, fq = lane >> 4;
+
+  // DMA of block b's rows m0 .. m0 + 127: thread x of load i writes chunk position p = 256 i + x.
+  // Rows past m are past the descriptor and read as zero.  (The thread index goes through an empty
+  // statement so that the offsets are formed at each use rather than kept across the loop.)
+  auto load_b = [&](int b, int buf) {
+    const __amdgpu_buffer_rsrc_t rs = make_rsrc(a.bp + (long long)b * a.m * 3 * RP, (unsigned)a.m * 3 * RP * 2);
+    int x = tid;
+    asm volatile("" : "+v"(x));
+#pragma unroll
+    for (int i = 0; i < ND; ++i) {
+      const int p = 256 * i + x, row = p / CH, c = (p % CH) ^ fan_swz<RPK>(row);
+      const unsigned off = (unsigned)(m0 + row) * (3 * RP * 2) + c * 16;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)(lds + buf * BUF + (256 * i + 64 * wave) * 16), 16, off,
+                                               0, 0, 0);
+    }
+  };
+  int b = blockIdx.y;
+  load_b(b, 0);
+  if (b + a.splits < a.nblk) load_b(b + a.splits, 1);
+
+  // P fragments of the wave's 64 tokens: hi (RPK k steps), then lo.
+  bf16x8 ph[4][RPK], pl[4][RPK];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const bf16_t* p = a.pp + (size_t)min(t0 + 64 * wt + 16 * i + fr, a.T - 1) * 3 * RP + 8 * fq;
+#pragma unroll
+    for (int k = 0; k < RPK; ++k) {
+      ph[i][k] = *(const bf16x8*)(p + 32 * k);
+      pl[i][k] = *(const bf16x8*)(p + 2 * RP + 32 * k);
+    }
+  }
+  // This lane's 4 columns, and the base of tokens 16 i + 4 fq + e at them (m % 8 == 0: all 4 in or out).
+  const int col = m0 + 64 * wm + 4 * fr;
+  f32x4 base[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int e = 0; e < 4; ++e)
+      base[i][e] = *(const f32x4*)(a.base + (size_t)min(t0 + 64 * wt + 16 * i + 4 * fq + e, a.T - 1) * a.m +
+                                   min(col, a.m - 4));
+  const unsigned rows = (unsigned)min(128, a.T - t0), pitch = (unsigned)a.m * OSZ;
+  const unsigned vo = col < a.m ? (unsigned)(64 * wt + 4 * fq) * pitch + (unsigned)col * OSZ : 0x80000000u;
+  // Fragment row 4 fr + j (tile j) of the wave's 64: fan_swz of it does not depend on j.
+  const int fs = fan_swz<RPK>(64 * wm + 4 * fr);
+  const char* const frow = lds + (64 * wm + 4 * fr) * ROWB;
+
+  wait_vm<0>();
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  for (int n = 0;; ++n) {
+    const char* const lb = frow + (n & 1) * BUF;
+    f32x4 d[4][4];  // [token tile i][column tile j]
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int j = 0; j < 4; ++j) d[i][j] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    // Segment s of the rank-r term: P_hi B_hi, P_hi B_lo, P_lo B_hi.
+#pragma unroll
+    for (int s = 0; s < 3; ++s)
+#pragma unroll
+      for (int k = 0; k < RPK; ++k) {
+        const int c = ((s == 1 ? RP / 8 : 0) + 4 * k + fq) ^ fs;
+        bf16x8 fb[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) fb[j] = *(const bf16x8*)(lb + j * ROWB + c * 16);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            d[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(s == 2 ? pl[i][k] : ph[i][k], fb[j], d[i][j], 0, 0, 0);
+      }
+    // Every wave is done reading this buffer: the block after next goes into it.
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    const bool more = b + 2 * a.splits < a.nblk;
+    if (more) load_b(b + 2 * a.splits, n & 1);
+    __builtin_amdgcn_sched_barrier(0);  // the loads are issued before the stores
+    const __amdgpu_buffer_rsrc_t ry = make_rsrc((char*)a.Y + ((long long)b * a.T + t0) * a.m * OSZ, rows * pitch);
+    unsigned vs = vo;  // as in load_b: offsets formed here, not kept
+    asm volatile("" : "+v"(vs));
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        f32x4 v;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          v[j] = d[i][j][e] + base[i][e][j];
+          if (a.relu) v[j] = fmaxf(v[j], 0.f);
+        }
+        const int off = (int)(vs + (unsigned)(16 * i + e) * pitch);
+        if constexpr (OUT == ZO_F32)
+          __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), ry, off, 0, NT);
+        else if constexpr (OUT == ZO_BF16)
+          __builtin_amdgcn_raw_buffer_store_b64((u32x2){pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])}, ry, off, 0, NT);
+        else
+          __builtin_amdgcn_raw_buffer_store_b64((u32x2){pack_f16x2(v[0], v[1]), pack_f16x2(v[2], v[3])}, ry, off, 0, NT);
+      }
+    b += a.splits;
+    if (b >= a.nblk) break;
+    // The next block's rows have landed: since their loads this wave has issued the stores of two
+    // blocks (of one, after the first, whose predecessors' loads were waited for) and `more`'s loads.
+    if (more) wait_vm<2 * NS + ND>();
+    else wait_vm<2 * NS>();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  }
+}
+
+template <int RPK>
+void launch_fan_out(const FanArgs& a, int out, dim3 grid, hipStream_t stream) {
+  if (out == ZO_F32) hipLaunchKernelGGL((k_fan<RPK, ZO_F32>), grid, dim3(256), 0, stream, a);
+  else if (out == ZO_F16) hipLaunchKernelGGL((k_fan<RPK, ZO_F16>), grid, dim3(256), 0, stream, a);
+  else hipLaunchKernelGGL((k_fan<RPK, ZO_BF16>), grid, dim3(256), 0, stream, a);
+}
+
+int launch_fan(FanArgs a, int rp, int out, hipStream_t stream) {
+  a.tiles_m = (a.m + 127) / 128;
+  a.tiles_t = (a.T + 127) / 128;
+  const long long total = (long long)a.tiles_m * a.tiles_t;
+  if (total > 0x7fffffffLL) {
+    zo_set_error("perturbed linear: too many tiles (%lld)", total);
+    return ZO_ERR_UNSUPPORTED;
+  }
+  a.total_tiles = (int)total;
+  // Two workgroups per CU: where the tiles are fewer, the blocks of a tile are shared out.
+  a.splits = (int)std::min<long long>(a.nblk, std::max<long long>(1, 512 / total));
+  const dim3 grid((unsigned)total, (unsigned)a.splits);
+  switch (rp / 32) {
+    case 1: launch_fan_out<1>(a, out, grid, stream); break;
+    case 2: launch_fan_out<2>(a, out, grid, stream); break;
+    case 3: launch_fan_out<3>(a, out, grid, stream); break;
+    default: launch_fan_out<4>(a, out, grid, stream); break;
+  }
+  return zo_hip_status(hipGetLastError(), "k_fan");
+}
+
 template <bool F16, int OUT>
 void launch_main_epi(const GemmArgs& a, dim3 grid, hipStream_t stream) {
   if constexpr (OUT != ZO_F32) {  // the projection epilogues write bf16 whatever OUT is
@@ -1278,11 +1474,7 @@ void launch_main_epi(const GemmArgs& a, dim3 grid, hipStream_t stream) {
       return;
     }
   }
-  if (a.epi == EPI_BASE)
-    hipLaunchKernelGGL((k_gemm_main<F16, OUT, EPI_BASE>), grid, dim3(256), 0, stream, a);
-  else if (a.epi == EPI_BASE_RELU)
-    hipLaunchKernelGGL((k_gemm_main<F16, OUT, EPI_BASE_RELU>), grid, dim3(256), 0, stream, a);
-  else if (a.epi == ZO_EPI_RELU)
+  if (a.epi == ZO_EPI_RELU)
     hipLaunchKernelGGL((k_gemm_main<F16, OUT, ZO_EPI_RELU>), grid, dim3(256), 0, stream, a);
   else if (a.epi == ZO_EPI_RESIDUAL)
     hipLaunchKernelGGL((k_gemm_main<F16, OUT, ZO_EPI_RESIDUAL>), grid, dim3(256), 0, stream, a);
@@ -1667,30 +1859,18 @@ static int apply_fan(const PlinearPlan& p, const PlinearWs& w, const void* X, co
   b.ldy = p.m;
   b.out_dtype = ZO_F32;
   b.epi = ZO_EPI_NONE;
-  GemmArgs h{};
-  h.A = (const bf16_t*)W;
-  h.B = (const bf16_t*)X;
-  h.rows_a = p.m;
-  h.rows_b = p.T;
-  h.K = 0;
-  h.nblk = p.nblk;
-  h.ca = (const bf16_t*)w.bp;
-  h.ca_block_stride = (long long)p.m * 3 * p.rp;
-  h.cb = (const bf16_t*)w.pp;
-  h.cb_block_stride = 0;
-  h.rc = 3 * p.rp;
-  h.Y = Y;
-  h.y_block_stride = (long long)p.T * p.m;
-  h.ldy = p.m;
-  h.out_dtype = p.out_dtype;
-  h.epi = epi == ZO_EPI_RELU ? EPI_BASE_RELU : EPI_BASE;
-  h.R = w.base;
-  h.r_block_stride = 0;
-  h.blk_inner = 1;
-  int st = launch_gemm_main(b, f16, stream);
+  const int st = launch_gemm_main(b, f16, stream);
   if (st != ZO_OK) return st;
-  // No main-segment tiles here (K = 0): f16 only selects the fp16 output type.
-  return launch_gemm_main(h, f16, stream);
+  FanArgs h{};
+  h.base = (const float*)w.base;
+  h.pp = (const bf16_t*)w.pp;
+  h.bp = (const bf16_t*)w.bp;
+  h.Y = Y;
+  h.T = p.T;
+  h.m = p.m;
+  h.nblk = p.nblk;
+  h.relu = epi == ZO_EPI_RELU;
+  return launch_fan(h, p.rp, p.out_dtype, stream);
 }
 
 static bool fan_fits(const PlinearPlan& p, int epi) {
@@ -1699,11 +1879,9 @@ static bool fan_fits(const PlinearPlan& p, int epi) {
   b.rows_a = p.m;
   b.rows_b = p.T;
   b.K = p.n;
-  GemmArgs h{};
-  h.rows_a = p.m;
-  h.rows_b = p.T;
-  h.rc = 3 * p.rp;
-  return main_gemm_fits(b) && main_gemm_fits(h);
+  // k_fan's descriptors: one block's B operand, and 128 rows of an output.
+  return main_gemm_fits(b) && (unsigned long long)p.m * 3 * p.rp * 2 <= (1ull << 31) &&
+         128ull * p.m * (p.out_dtype == ZO_F32 ? 4 : 2) <= (1ull << 31);
 }
 
 int zo_plinear_apply(const PlinearPlan& p, const void* X, const void* W, void* Y, void* ws,
