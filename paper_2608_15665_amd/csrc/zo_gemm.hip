@@ -12,8 +12,8 @@
 //   3. projection    : P = X_x Vt2_hi^T + X_x Vt2_lo^T of every distinct X block,
 //                      written as the K segment [P_hi | P_hi | P_lo] (bf16,
 //                      3 rp wide).  k_proj for one factor of 64 or 128 rows
-//                      (or a pair of 64), the main GEMM with the EPI_PROJ
-//                      epilogues for a stack of factors that read the same X;
+//                      (or two or three of 64), the main GEMM with the EPI_PROJ
+//                      epilogues for a wider stack of factors that read the same X;
 //                      otherwise an fp32 projection followed by k_pcombine.
 //   4. main GEMM     : Y_b = X_b W^T + P_{x(b)} B_b^T, the rank-r term added as
 //                      one more 3 rp-deep K segment into the same fp32
@@ -1084,22 +1084,21 @@ __global__ __launch_bounds__(256, 1) void k_gemm_main(GemmArgs a) {
 // of a stack of `count` (each 2 RP rows of Vt2: the hi rows, then the lo rows),
 //   P = (X_b Vt2_hi^T + X_b Vt2_lo^T) * unscale,  written as [P_hi | P_hi | P_lo] (bf16, 3 RP),
 // which is the left operand of the fused GEMM's rank-r segment.  The projection reads every X
-// block once and is bound by that stream, so the tile is narrow: 256 tokens x 128 factor rows
-// per workgroup, the 4 waves side by side along the tokens (64 tokens x 128 rows each, 8 x 4
-// accumulators of the 16x16x32 MFMA), so a k-tile's MFMAs (1024 cycles per wave) take less time
-// than its 32 KB of X takes to arrive.  A factor's hi and lo rows lie in the same tile and the
+// block once and is bound by that stream, so the tile is narrow: TT tokens x all ROWS = 2 RP NF
+// rows of NF factors per workgroup, the 4 waves side by side along the tokens (TT / 4 tokens x ROWS
+// each).  A factor's hi and lo rows lie in the same tile and the
 // same lane (accumulators i and i + RP / 16), so the combine, the hi/lo split and the rounding
 // happen in registers and the fp32 projection never goes to memory.  Every accumulator sums
 // its k terms in ascending order, 32 at a time, as in the main GEMM: the values are those of
 // the unfused projection followed by the separate combine.
 //
-// K is walked in tiles of 64 through a 3-stage LDS ring (X part 32 KB, factor part 16 KB per
-// stage; rows swizzled as in the main GEMM), filled by direct global->LDS loads two tiles ahead,
-// with one barrier per tile.  Rows past T or past the stack are loaded from the last valid row
-// and not stored.
-constexpr int PJ_XPART = 256 * 128;
-constexpr int PJ_STAGE = PJ_XPART + 128 * 128;
-
+// K is walked in tiles of 64 through an NST-stage LDS ring (TT X rows and ROWS factor rows of 128
+// bytes per stage; rows swizzled as in the main GEMM), filled by direct global->LDS loads NST - 1
+// tiles ahead, with one barrier per tile.  Rows past T or past the stack are loaded from the last
+// valid row and not stored.  K a multiple of 8 only: the last tile's chunks past K are given an
+// offset out of range and read as zero.
+//
+// TT: see launch_proj_fused.
 struct ProjArgs {
   const bf16_t* V;           // rows_v x K: the stacked Vt2 of `count` factors
   const bf16_t* X;           // per block T x K
@@ -1110,12 +1109,32 @@ struct ProjArgs {
   bf16_t* pc[ZO_MAX_GROUP];  // factor f's output: (nx T) x 3 RP
 };
 
-template <bool F16, int RP>
-__global__ __launch_bounds__(256, 1) void k_proj(ProjArgs a) {
+// s_waitcnt vmcnt(N).
+template <int N>
+__device__ __forceinline__ void wait_vm() {
+  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+// Accumulators whose zeros are in place 2 wait states before anything after this statement.
+__device__ __forceinline__ void fence_zero(f32x4& a) { asm volatile("s_nop 1" : "+a"(a)); }
+__device__ __forceinline__ void fence_zero(f32x4& a, f32x4& b) { asm volatile("s_nop 1" : "+a"(a), "+a"(b)); }
+__device__ __forceinline__ void fence_zero(f32x4& a, f32x4& b, f32x4& c) {
+  asm volatile("s_nop 1" : "+a"(a), "+a"(b), "+a"(c));
+}
+__device__ __forceinline__ void fence_zero(f32x4& a, f32x4& b, f32x4& c, f32x4& d) {
+  asm volatile("s_nop 1" : "+a"(a), "+a"(b), "+a"(c), "+a"(d));
+}
+// An accumulator that is written before this statement and not read or copied ahead of it.
+__device__ __forceinline__ void fence_read(f32x4& a) { asm volatile("" : "+a"(a)); }
+
+template <bool F16, int RP, int NF, int TT, int NST>
+__global__ __launch_bounds__(256, 160 * 1024 / (NST * (TT + 2 * RP * NF) * 128) >= 2 ? 2 : 1) void k_proj(ProjArgs a) {
   static_assert(RP == 32 || RP == 64, "factors of 64 or 128 rows");
-  constexpr int NF = 128 / (2 * RP);  // factors per tile
-  constexpr int R16 = RP / 16;
-  __shared__ __attribute__((aligned(1024))) char lds[3 * PJ_STAGE];
+  constexpr int ROWS = 2 * RP * NF, R16 = RP / 16;
+  constexpr int NI = ROWS / 16, NJ = TT / 64;         // 16-row and 16-token groups of a wave
+  constexpr int XPART = TT * 128, STAGE = XPART + ROWS * 128;
+  constexpr int LX = TT / 32, LV = ROWS / 32, NLD = LX + LV;  // loads per wave per tile
+  __shared__ __attribute__((aligned(1024))) char lds[NST * STAGE];
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // XCD-aware order; the factor tiles of one token tile are adjacent, so its X tile comes
@@ -1126,101 +1145,128 @@ __global__ __launch_bounds__(256, 1) void k_proj(ProjArgs a) {
   const int ct = __builtin_amdgcn_readfirstlane(lt % a.tiles_c);
   const int bt = lt / a.tiles_c;
   const int blk = __builtin_amdgcn_readfirstlane(bt / a.tiles_t);
-  const int t0 = __builtin_amdgcn_readfirstlane((bt % a.tiles_t) * 256);
-  const int c0 = ct * 128;
+  const int t0 = __builtin_amdgcn_readfirstlane((bt % a.tiles_t) * TT);
+  const int c0 = ct * ROWS;
   const __amdgpu_buffer_rsrc_t rsX =
       make_rsrc(a.X + (long long)blk * a.x_block_stride, (unsigned)a.T * a.K * 2);
   const __amdgpu_buffer_rsrc_t rsV = make_rsrc(a.V, (unsigned)a.rows_v * a.K * 2);
-  // DMA: load i of a wave writes rows 8 (wave + 4 i) .. + 7 of a part (8 loads for the 256 X
-  // rows, 4 for the 128 factor rows); lane l writes row l / 8 at physical chunk l % 8.
+  // DMA: load i of a wave writes rows 8 (wave + 4 i) .. + 7 of a part; lane l writes row l / 8 at
+  // physical chunk l % 8.
   const int drow = lane >> 3;
   const int lch = (lane & 7) ^ f8(8 * wave + drow);
-  unsigned voX[8], voV[4];
+  unsigned voX[LX], voV[LV];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) voX[i] = dma_off(t0 + 8 * (wave + 4 * i) + drow, a.T, a.K, lch);
+  for (int i = 0; i < LX; ++i) voX[i] = dma_off(t0 + 8 * (wave + 4 * i) + drow, a.T, a.K, lch);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) voV[i] = dma_off(c0 + 8 * (wave + 4 * i) + drow, a.rows_v, a.K, lch);
+  for (int i = 0; i < LV; ++i) voV[i] = dma_off(c0 + 8 * (wave + 4 * i) + drow, a.rows_v, a.K, lch);
   char* const ldsw = lds + 8 * wave * 128;
+  const int NT = (a.K + 63) / 64;
   auto load = [&](int st, int t) {
-    char* d = ldsw + st * PJ_STAGE;
+    char* d = ldsw + st * STAGE;
     const unsigned so = (unsigned)t * 128u;
+    // Past K in a ragged last tile: out of range (every span is then below 2^31 bytes).
+    const unsigned oob = (a.K & 31) != 0 && t * 64 + lch * 8 >= a.K ? 0x80000000u : 0u;
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsX, (lds_ptr_t)(d + 32 * 128 * i), 16, voX[i], so, 0, 0);
+    for (int i = 0; i < LX; ++i) {
+      const unsigned off = voX[i] | oob;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsX, (lds_ptr_t)(d + 32 * 128 * i), 16, off, so, 0, 0);
+    }
 #pragma unroll
-    for (int i = 0; i < 4; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsV, (lds_ptr_t)(d + PJ_XPART + 32 * 128 * i), 16, voV[i], so,
-                                               0, 0);
+    for (int i = 0; i < LV; ++i) {
+      const unsigned off = voV[i] | oob;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rsV, (lds_ptr_t)(d + XPART + 32 * 128 * i), 16, off, so, 0, 0);
+    }
   };
-  // Fragments of substep s: factor rows 16 i + l % 16 (A operand, i < 8) and the wave's tokens
-  // 64 wave + 16 j + l % 16 (B operand, j < 4), chunk 4 s + l / 16.
+  // Fragments of substep s: factor rows 16 i + l % 16 (A operand) and the wave's tokens
+  // TT / 4 wave + 16 j + l % 16 (B operand), chunk 4 s + l / 16.
   const int fr = lane & 15, fq = lane >> 4;
   const int ff = f8(fr);
   auto frags = [&](int st, int s, bf16x8* fa, bf16x8* fb) {
     const int ch = ((4 * s + fq) ^ ff) * 16;
-    const char* pv = lds + st * PJ_STAGE + PJ_XPART + fr * 128 + ch;
-    const char* px = lds + st * PJ_STAGE + (wave * 64 + fr) * 128 + ch;
+    const char* pv = lds + st * STAGE + XPART + fr * 128 + ch;
+    const char* px = lds + st * STAGE + (wave * (TT / 4) + fr) * 128 + ch;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) fa[i] = *(const bf16x8*)(pv + i * 16 * 128);
+    for (int i = 0; i < NI; ++i) fa[i] = *(const bf16x8*)(pv + i * 16 * 128);
 #pragma unroll
-    for (int j = 0; j < 4; ++j) fb[j] = *(const bf16x8*)(px + j * 16 * 128);
+    for (int j = 0; j < NJ; ++j) fb[j] = *(const bf16x8*)(px + j * 16 * 128);
   };
-  // acc[i][j]: factor rows 16 i + 4 (l / 16) .. + 3 of the tile, token 64 wave + 16 j + l % 16.
-  f32x4 acc[8][4];
+  // acc[i][j]: factor rows 16 i + 4 (l / 16) .. + 3 of the tile, token TT / 4 wave + 16 j + l % 16.
+  f32x4 acc[NI][NJ];
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
+  for (int i = 0; i < NI; ++i)
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < NJ; ++j)
 #pragma unroll
       for (int e = 0; e < 4; ++e) acc[i][j][e] = 0.f;
+  // The zeros in place 2 wait states before the first MFMA: 8 fences, FI accumulators each.
+  constexpr int NA = NI * NJ, FI = (NA + 7) / 8;
+  static_assert(FI >= 1 && FI <= 4, "a fence ties up to 4 accumulators");
+  auto flat = [&](int x) -> f32x4& { return acc[x % NA / NJ][x % NA % NJ]; };
 #pragma unroll
-  for (int i = 0; i < 8; ++i)  // the zeros in place 2 wait states before the first MFMA
-    asm volatile("s_nop 1" : "+a"(acc[i][0]), "+a"(acc[i][1]), "+a"(acc[i][2]), "+a"(acc[i][3]));
+  for (int x = 0; x < NA; ++x) fence_read(flat(x));  // every zero is written before the first fence
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    if constexpr (FI == 1) fence_zero(flat(i));
+    else if constexpr (FI == 2) fence_zero(flat(2 * i), flat(2 * i + 1));
+    else if constexpr (FI == 3) fence_zero(flat(3 * i), flat(3 * i + 1), flat(3 * i + 2));
+    else fence_zero(flat(4 * i), flat(4 * i + 1), flat(4 * i + 2), flat(4 * i + 3));
+  }
   auto mma = [&](const bf16x8* fa, const bf16x8* fb) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i)
+    for (int i = 0; i < NI; ++i)
 #pragma unroll
-      for (int j = 0; j < 4; ++j) mfma16<F16>(acc[i][j], fa[i], fb[j]);
+      for (int j = 0; j < NJ; ++j) mfma16<F16>(acc[i][j], fa[i], fb[j]);
   };
 
-  const int NT = (a.K + 63) / 64;
-  const bool half = (a.K & 63) != 0;  // the last tile holds 32 valid columns
-  load(0, 0);
-  if (NT > 1) {
-    load(1, 1);
-    asm volatile("s_waitcnt vmcnt(12)" ::: "memory");  // this wave's loads of tile 0 landed
-  } else {
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  }
+  const bool half = (a.K & 63) != 0 && (a.K & 63) <= 32;  // the last tile's second half is empty
+#pragma unroll
+  for (int t = 0; t < NST - 1; ++t)
+    if (t < NT) load(t, t);
+  // Tile t's loads have landed when only those of the `ahead` later tiles may be in flight.
+  auto landed = [&](int ahead) {
+    if (NST > 3 && ahead >= 2) wait_vm<NST >= 4 ? 2 * NLD : 0>();
+    else if (NST > 2 && ahead == 1) wait_vm<NST >= 3 ? NLD : 0>();
+    else wait_vm<0>();
+  };
+  static_assert(NST >= 2 && NST <= 4, "landed() counts at most two tiles ahead");
+  landed(min(NT - 1, NST - 2));
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
-  // Tile t (both 32-deep substeps, or only the first for the last tile of an odd K / 32).
-  auto tile = [&](int t, bool two) {
-    const int st = t % 3;
-    if (t + 2 < NT) load((t + 2) % 3, t + 2);  // into the stage tile t - 1 vacated
-    bf16x8 fa[8], fb[4], ga[8], gb[4];
+  // Tile t in stage st (both 32-deep substeps, or only the first where the second is empty).
+  auto tile = [&](int t, int st, bool two) {
+    const int fill = st == 0 ? NST - 1 : st - 1;  // the stage tile t - 1 vacated
+    if (t + NST - 1 < NT) load(fill, t + NST - 1);
+    bf16x8 fa[NI], fb[NJ], ga[NI], gb[NJ];
     frags(st, 0, fa, fb);
     if (two) frags(st, 1, ga, gb);
     mma(fa, fb);
     if (two) mma(ga, gb);
-    // Tile t + 1 landed (only tile t + 2's loads may be in flight) and this wave's reads of
-    // stage st are done; after the barrier every wave may overwrite it.
-    if (t + 2 < NT)
-      asm volatile("s_waitcnt vmcnt(12) lgkmcnt(0)" ::: "memory");
-    else
-      asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    // Tile t + 1 landed and this wave's reads of stage st are done; after the barrier every wave
+    // may overwrite it.
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    landed(min(NT - 1, t + NST - 1) - (t + 1));
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
   };
+  // UN tiles per trip, the stages constants.
+  constexpr int UN = NST * (NA <= 4 ? 3 : 1);
   const int NTF = half ? NT - 1 : NT;
-  for (int t = 0; t < NTF; ++t) tile(t, true);
-  if (half) tile(NT - 1, false);
+  int t = 0;
+  for (; t + UN <= NTF; t += UN) {
+#pragma unroll
+    for (int u = 0; u < UN; ++u) tile(t + u, u % NST, true);
+  }
+  int st = 0;
+  for (; t < NTF; ++t) {
+    tile(t, st, true);
+    st = st == NST - 1 ? 0 : st + 1;
+  }
+  if (half) tile(NT - 1, st, false);
   // 24 wait states after the last MFMA, then the accumulators pass through tied empty
   // statements so that no read of them is placed ahead of the wait.
   asm volatile("s_nop 7\n\ts_nop 7\n\ts_nop 7" ::: "memory");
 #pragma unroll
-  for (int i = 0; i < 8; ++i)
-    asm volatile("" : "+a"(acc[i][0]), "+a"(acc[i][1]), "+a"(acc[i][2]), "+a"(acc[i][3]));
+  for (int x = 0; x < NA; ++x) fence_read(flat(x));
 
 #pragma unroll
   for (int f = 0; f < NF; ++f) {
@@ -1228,8 +1274,8 @@ __global__ __launch_bounds__(256, 1) void k_proj(ProjArgs a) {
     if (gf >= a.count) break;
     bf16_t* const pc = a.pc[gf];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int tok = t0 + wave * 64 + 16 * j + fr;
+    for (int j = 0; j < NJ; ++j) {
+      const int tok = t0 + wave * (TT / 4) + 16 * j + fr;
       if (tok >= a.T) continue;
       bf16_t* const o = pc + ((long long)blk * a.T + tok) * (3 * RP) + 4 * fq;
 #pragma unroll
@@ -1293,12 +1339,6 @@ struct FanArgs {
 template <int RPK>
 __device__ __forceinline__ int fan_swz(int row) {
   return (row >> 2) & (RPK % 2 ? 7 : 15);
-}
-
-// s_waitcnt vmcnt(N), for the counts k_fan needs.
-template <int N>
-__device__ __forceinline__ void wait_vm() {
-  asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
 }
 
 template <int RPK, int OUT>
@@ -1517,6 +1557,51 @@ int launch_gemm_main(GemmArgs a, bool f16, hipStream_t stream) {
   return zo_hip_status(hipGetLastError(), "k_gemm_main");
 }
 
+template <bool F16, int RP, int NF, int TT, int NST>
+int launch_proj(ProjArgs a, int nx, hipStream_t stream) {
+  a.tiles_t = (a.T + TT - 1) / TT;
+  a.tiles_c = (a.rows_v + 2 * RP * NF - 1) / (2 * RP * NF);
+  const long long total = (long long)nx * a.tiles_t * a.tiles_c;
+  if (total <= 0) return ZO_OK;
+  if (total > 0x7fffffffLL) {
+    zo_set_error("perturbed linear: too many projection tiles (%lld)", total);
+    return ZO_ERR_UNSUPPORTED;
+  }
+  a.total_tiles = (int)total;
+  hipLaunchKernelGGL((k_proj<F16, RP, NF, TT, NST>), dim3((unsigned)total), dim3(256), 0, stream, a);
+  return zo_hip_status(hipGetLastError(), "k_proj");
+}
+
+// Tokens per tile.  A projection is bound by its X stream: 256-token tiles read the factor rows
+// once per 256 tokens and are best when they fill the chip, but at one workgroup per CU 128 of them
+// stream on half the CUs.  256 tiles of 128 tokens, or any number of 64-token tiles otherwise, keep
+// more loads in flight.  Whole prepare, us, 256 / 128 / 64 tokens per tile:
+//   r = 64: 16 x 8192 x 5120: 289 / 313 / 371;  8 x 4096 x 2048: 55 / 41 / 40;
+//           4 x 8192 x 20480: 373 / 288 / 343;  8192 x 5120: 106 / 69 / 52
+//   r = 32: 8 x 4096 x 5120: 94 / 73 / 81;      9 x 1000 x 2056: 38 / 26 / 22
+//   two factors of r = 32: 8 x 4096 x 4096: 85 / 61 / 69
+//   three: 77 (128), 88 (64), main GEMM 94;     16 x 8192 x 5120: 352 (128), main GEMM 302
+template <bool F16>
+int launch_proj_pick(const ProjArgs& a, int rp, int nx, hipStream_t stream) {
+  const bool many = (long long)nx * ((a.T + 255) / 256) >= 256, some = (long long)nx * ((a.T + 127) / 128) >= 256;
+  if (rp == 64) {
+    if (many) return launch_proj<F16, 64, 1, 256, 3>(a, nx, stream);
+    if (some) return launch_proj<F16, 64, 1, 128, 4>(a, nx, stream);
+    return launch_proj<F16, 64, 1, 64, 3>(a, nx, stream);
+  }
+  if (a.count == 1) {
+    if (some) return launch_proj<F16, 32, 1, 128, 3>(a, nx, stream);
+    return launch_proj<F16, 32, 1, 64, 3>(a, nx, stream);
+  }
+  if (a.count == 2) {
+    if (many) return launch_proj<F16, 32, 2, 256, 3>(a, nx, stream);
+    if (some) return launch_proj<F16, 32, 2, 128, 4>(a, nx, stream);
+    return launch_proj<F16, 32, 2, 64, 3>(a, nx, stream);
+  }
+  if (some) return launch_proj<F16, 32, 3, 128, 3>(a, nx, stream);
+  return launch_proj<F16, 32, 3, 64, 2>(a, nx, stream);
+}
+
 }  // namespace
 
 int zo_plinear_plan(PlinearPlan* p, int T, int m, int n, int r, int q, int nblk,
@@ -1700,10 +1785,10 @@ static int launch_proj_main(const PlinearPlan& p, const void* X, const void* vt,
 }
 
 // The fused projection (k_proj): 16-bit factors of 64 or 128 rows (rp = 32 or 64), each
-// operand's buffer descriptor below 2^32 bytes.
+// operand's buffer descriptor below 2^32 bytes (2^31 where K is no multiple of 32).
 static bool proj_fused_fits(const PlinearPlan& p, int count) {
-  const unsigned long long lim = (1ull << 32) - 256;
-  return p.in16 && (p.rp == 32 || p.rp == 64) && p.n % 32 == 0 && count >= 1 && count <= ZO_MAX_GROUP &&
+  const unsigned long long lim = p.n % 32 ? (1ull << 31) : (1ull << 32) - 256;
+  return p.in16 && (p.rp == 32 || p.rp == 64) && p.n % 8 == 0 && count >= 1 && count <= ZO_MAX_GROUP &&
          (unsigned long long)p.T * p.n * 2 <= lim && (unsigned long long)count * 2 * p.rp * p.n * 2 <= lim;
 }
 
@@ -1719,27 +1804,10 @@ static int launch_proj_fused(const PlinearPlan& p, const void* X, const void* vt
   a.T = p.T;
   a.K = p.n;
   a.count = count;
-  a.tiles_t = (p.T + 255) / 256;
-  a.tiles_c = (a.rows_v + 127) / 128;
-  const long long total = (long long)p.nx * a.tiles_t * a.tiles_c;
-  if (total <= 0) return ZO_OK;
-  if (total > 0x7fffffffLL) {
-    zo_set_error("perturbed linear: too many projection tiles (%lld)", total);
-    return ZO_ERR_UNSUPPORTED;
-  }
-  a.total_tiles = (int)total;
   a.unscale = p.in_dtype == ZO_F16 ? 1.f / ZO_F16_RSCALE : 1.f;
   for (int i = 0; i < count; ++i) a.pc[i] = pc[i];
-  const dim3 grid((unsigned)total);
-  const bool f16 = p.in_dtype == ZO_F16;
-  if (p.rp == 32) {
-    if (f16) hipLaunchKernelGGL((k_proj<true, 32>), grid, dim3(256), 0, stream, a);
-    else hipLaunchKernelGGL((k_proj<false, 32>), grid, dim3(256), 0, stream, a);
-  } else {
-    if (f16) hipLaunchKernelGGL((k_proj<true, 64>), grid, dim3(256), 0, stream, a);
-    else hipLaunchKernelGGL((k_proj<false, 64>), grid, dim3(256), 0, stream, a);
-  }
-  return zo_hip_status(hipGetLastError(), "k_proj");
+  return p.in_dtype == ZO_F16 ? launch_proj_pick<true>(a, p.rp, p.nx, stream)
+                              : launch_proj_pick<false>(a, p.rp, p.nx, stream);
 }
 
 size_t zo_plinear_group_ws(const PlinearPlan& p, int count) {
@@ -1774,12 +1842,15 @@ int zo_plinear_prepare_group(const PlinearPlan* plans, int count, const int* blk
   }
   if ((st = launch_transpose_v(plans, count, V, vts, stream)) != ZO_OK) return st;
   if ((st = launch_bprime(plans, count, tab, eps, U, Z, bps, stream)) != ZO_OK) return st;
-  // A stack of several factors stays on the main GEMM's 256-row tiles (two factors of 128 rows
-  // per X tile: the stacked q, k, v run 0.50 ms there against 0.72 ms in three 128-row tiles of
-  // k_proj), with the combine in its epilogue; only a 64-row pair shares one 128-row tile.
+  // Up to 128 rows in all go to k_proj, and three factors of 64 rows while its 256-token tiles
+  // would not fill the chip; other stacks stay on the main GEMM's 256-row tiles (two factors of 128
+  // rows per X tile: the stacked q, k, v run 0.50 ms there against 0.72 ms in three 128-row tiles of
+  // k_proj), with the combine in its epilogue.
   bf16_t* pc[ZO_MAX_GROUP];
   for (int i = 0; i < count; ++i) pc[i] = (bf16_t*)zo_plinear_ws(plans[i], ws[i]).pp;
-  if (2 * p0.rp * count <= 128 && proj_fused_fits(p0, count)) return launch_proj_fused(p0, X, gvt, count, pc, stream);
+  const bool few = (long long)p0.nx * ((p0.T + 255) / 256) < 256;
+  if (2 * p0.rp * count <= (few && count == 3 ? 192 : 128) && proj_fused_fits(p0, count))
+    return launch_proj_fused(p0, X, gvt, count, pc, stream);
   if (proj_main_fits(p0, count)) return launch_proj_main(p0, X, gvt, count, pc, stream);
   if ((st = launch_projection(p0, X, gvt, count * w2, gp2, stream)) != ZO_OK) return st;
   for (int i = 0; i < count; ++i)
