@@ -30,8 +30,8 @@
 // (zo_gemm_f32.hip).
 //
 // The main GEMM (k_gemm_main) is described where it is defined.  The
-// register-staged GEMM (k_gemm_bf16: the projection of wide factors and the
-// fallback when K is not a multiple of 32) computes a BM x BN tile of Y_b^T
+// register-staged GEMM (k_gemm_bf16: narrow projections k_proj does not take and
+// the fallback for operands beyond the main GEMM's descriptors) computes a BM x BN tile of Y_b^T
 // with v_mfma_f32_32x32x16_bf16: the A operand is the W tile (rows = output
 // columns), the B operand the X tile (rows = tokens), both K-contiguous and
 // staged through LDS in 128-byte rows with an XOR swizzle of the 16-byte
@@ -603,7 +603,7 @@ int launch_gemm_bf16(GemmArgs a, hipStream_t stream) {
 
 
 // ---------------------------------------------------------------------------
-// Main GEMM for K % 32 == 0: the kernel every model-shaped call takes.
+// Main GEMM: the kernel every call takes whose operands its buffer descriptors can span.
 //
 // 256 x 256 output tile per workgroup of 4 waves (one per SIMD), each wave a 128 x 128
 // sub-tile held in 64 accumulators of the 16x16x32 MFMA (256 AGPRs, updated in place).
@@ -630,8 +630,10 @@ int launch_gemm_bf16(GemmArgs a, hipStream_t stream) {
 //
 // The rank-rc correction is rc/64 more k-tiles through the same pipeline, with the A operand
 // taken from ca (per block, rows_a x rc) and the B operand from cb (per block, rows_b x rc).
-// The last tile of a segment whose length is an odd multiple of 32 holds 32 valid columns: only
-// its first substep is computed (the other half of its rows is loaded but never read).  So
+// The last tile of a segment that ends within a tile's first 32 columns: only
+// its first substep is computed (the other half of its rows is loaded but never read).  RAG: K is
+// a multiple of 8 only; the last main tile's chunks past K get an offset out of range and are read
+// as zero, in both operands (9 x 1003 x 3080 x 2056 with its projection: 203 -> 134 us against the register-staged kernel).  So
 // every accumulator sees its k terms in ascending order, 32 at a time, whatever the tiling.
 // Rows past rows_a / rows_b are loaded from the last valid row (never stored).  F16: the main
 // tiles run the fp16 MFMA and the correction tiles (bf16 hi/lo operands) the bf16 MFMA.  OUT
@@ -641,7 +643,8 @@ int launch_gemm_bf16(GemmArgs a, hipStream_t stream) {
 // which it stored wrongly).
 //
 // Each operand's buffer descriptor spans its rows x K (or rc) elements, so the host takes this
-// kernel only when every such span is below 2^32 bytes.
+// kernel only when every such span is below 2^32 bytes (2^31 for RAG, whose out-of-range offset is
+// 2^31).
 constexpr int MAIN_RB = 128;               // bytes per LDS row (64 bf16)
 constexpr int MAIN_PART = 256 * MAIN_RB;   // one part of a tile: 32 KB
 constexpr int MAIN_SLOTS = 5;
@@ -658,7 +661,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, un
   return __builtin_amdgcn_make_buffer_rsrc((void*)base, (short)0, (int)bytes, 0x00020000);
 }
 
-template <bool F16, int OUT, int EPI>
+template <bool F16, int OUT, int EPI, bool RAG = false>
 __global__ __launch_bounds__(256, 1) void k_gemm_main(GemmArgs a) {
   constexpr int RB = MAIN_RB, PART = MAIN_PART;
   __shared__ __attribute__((aligned(1024))) char lds[MAIN_SLOTS * PART];
@@ -684,7 +687,7 @@ __global__ __launch_bounds__(256, 1) void k_gemm_main(GemmArgs a) {
 
   // Tiles: main segment [0, NTM) over K, rank-rc segment [NTM, NT) over rc.
   const int NTM = (a.K + 63) / 64, NT = NTM + (a.rc + 63) / 64;
-  const bool halfM = (a.K & 63) != 0, halfR = (a.rc & 63) != 0;
+  const bool halfM = (a.K & 63) != 0 && (a.K & 63) <= 32, halfR = (a.rc & 63) != 0;
   const bf16_t* const Bblk = a.B + (long long)blk * a.b_block_stride;
   const bf16_t* const Cblk = a.ca + (long long)blk * a.ca_block_stride;
   const bf16_t* const Dblk = a.cb + (long long)blk * a.cb_block_stride;
@@ -708,6 +711,8 @@ __global__ __launch_bounds__(256, 1) void k_gemm_main(GemmArgs a) {
 #define voC(i) dma_off(m0 + 8 * (wave + 4 * (i)) + drow, a.rows_a, a.rc, lch)
 #define voD(i) dma_off(t0 + 8 * (wave + 4 * (i)) + drow, a.rows_b, a.rc, lch)
   char* const ldsw = lds + 8 * wave * RB;
+  // RAG: offset bits of this lane's chunk of main tile t, out of range past K.
+  auto past = [&](int t) -> unsigned { return RAG && t < NTM && t * 64 + lch * 8 >= a.K ? 0x80000000u : 0u; };
   // Loads i in [I0, I1) of part A (W rows) or B (X rows) of tile t into slot sl; tiles past the
   // end are not loaded.  MAIN: t is known to be a main-segment tile.  The rank segment's
   // descriptor is built after its base is chosen (a scalar select), so it stays in scalar
@@ -717,20 +722,20 @@ __global__ __launch_bounds__(256, 1) void k_gemm_main(GemmArgs a) {
     if (!m && t >= NT) return;
     char* d = ldsw + sl * PART;
     const __amdgpu_buffer_rsrc_t r = m ? rsA : make_rsrc(Cblk, (unsigned)a.rows_a * a.rc * 2);
-    const unsigned so = (unsigned)(m ? t : t - NTM) * 128u;
+    const unsigned so = (unsigned)(m ? t : t - NTM) * 128u, oob = past(t);
 #pragma unroll
     for (int i = decltype(I0)::value; i < decltype(I1)::value; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr_t)(d + 32 * RB * i), 16, m ? voA[i] : voC(i), so, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr_t)(d + 32 * RB * i), 16, m ? voA[i] | oob : voC(i), so, 0, 0);
   };
   auto load_B = [&](int sl, int t, auto MAIN, auto I0, auto I1) {
     const bool m = decltype(MAIN)::value || t < NTM;
     if (!m && t >= NT) return;
     char* d = ldsw + sl * PART;
     const __amdgpu_buffer_rsrc_t r = m ? rsB : make_rsrc(Dblk, (unsigned)a.rows_b * a.rc * 2);
-    const unsigned so = (unsigned)(m ? t : t - NTM) * 128u;
+    const unsigned so = (unsigned)(m ? t : t - NTM) * 128u, oob = past(t);
 #pragma unroll
     for (int i = decltype(I0)::value; i < decltype(I1)::value; ++i)
-      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr_t)(d + 32 * RB * i), 16, m ? voB[i] : voD(i), so, 0, 0);
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_ptr_t)(d + 32 * RB * i), 16, m ? voB[i] | oob : voD(i), so, 0, 0);
   };
   using Main = std::true_type;
   using Any = std::false_type;
@@ -847,13 +852,15 @@ __global__ __launch_bounds__(256, 1) void k_gemm_main(GemmArgs a) {
   const __amdgpu_buffer_rsrc_t rsD = make_rsrc(Dblk, (unsigned)a.rows_b * a.rc * 2);
   auto load1g_A = [&](int sl, int t, int i) {
     const bool m = t < NTM;
+    const unsigned off = m ? voA[i] | past(t) : voC(i);
     __builtin_amdgcn_raw_ptr_buffer_load_lds(m ? rsA : rsC, (lds_ptr_t)(ldsw + sl * PART + 32 * RB * i), 16,
-                                             m ? voA[i] : voC(i), (unsigned)(m ? t : t - NTM) * 128u, 0, 0);
+                                             off, (unsigned)(m ? t : t - NTM) * 128u, 0, 0);
   };
   auto load1g_B = [&](int sl, int t, int i) {
     const bool m = t < NTM;
+    const unsigned off = m ? voB[i] | past(t) : voD(i);
     __builtin_amdgcn_raw_ptr_buffer_load_lds(m ? rsB : rsD, (lds_ptr_t)(ldsw + sl * PART + 32 * RB * i), 16,
-                                             m ? voB[i] : voD(i), (unsigned)(m ? t : t - NTM) * 128u, 0, 0);
+                                             off, (unsigned)(m ? t : t - NTM) * 128u, 0, 0);
   };
   // Tile k as body_main, with run-time slots and loads from either segment: the tiles that
   // follow the unrolled main loop (the last main tiles and the rank segment), up to NT - 3.
@@ -889,8 +896,10 @@ __global__ __launch_bounds__(256, 1) void k_gemm_main(GemmArgs a) {
     if (!half) mma(F1a, F1b, f16);
   };
   using MT = std::integral_constant<bool, F16>;
-  // body_main needs k + 2 <= NTM - 1 (main-segment loads) and tile k full: k <= NTM - 3.
-  const int P = NTM >= 3 ? (NTM - 2) / 5 * 5 : 0;
+  // body_main needs k + 2 <= NTM - 1 (main-segment loads) and tile k full: k <= NTM - 3; its loads
+  // do not look at K, so with a ragged last tile k + 2 <= NTM - 2.
+  constexpr int LAST = RAG ? 3 : 2;
+  const int P = NTM > LAST ? (NTM - LAST) / 5 * 5 : 0;
   int k = 0;
   for (; k < P; k += 5) {
     body_main(k, std::integral_constant<int, 0>{}, MT{});
@@ -1502,6 +1511,18 @@ int launch_fan(FanArgs a, int rp, int out, hipStream_t stream) {
   return zo_hip_status(hipGetLastError(), "k_fan");
 }
 
+template <bool F16, int OUT, bool RAG>
+void launch_main_rag(const GemmArgs& a, dim3 grid, hipStream_t stream) {
+  if (a.epi == ZO_EPI_RELU)
+    hipLaunchKernelGGL((k_gemm_main<F16, OUT, ZO_EPI_RELU, RAG>), grid, dim3(256), 0, stream, a);
+  else if (a.epi == ZO_EPI_RESIDUAL)
+    hipLaunchKernelGGL((k_gemm_main<F16, OUT, ZO_EPI_RESIDUAL, RAG>), grid, dim3(256), 0, stream, a);
+  else if (a.epi == ZO_EPI_SILU_MUL)
+    hipLaunchKernelGGL((k_gemm_main<F16, OUT, ZO_EPI_SILU_MUL, RAG>), grid, dim3(256), 0, stream, a);
+  else
+    hipLaunchKernelGGL((k_gemm_main<F16, OUT, ZO_EPI_NONE, RAG>), grid, dim3(256), 0, stream, a);
+}
+
 template <bool F16, int OUT>
 void launch_main_epi(const GemmArgs& a, dim3 grid, hipStream_t stream) {
   if constexpr (OUT != ZO_F32) {  // the projection epilogues write bf16 whatever OUT is
@@ -1514,21 +1535,17 @@ void launch_main_epi(const GemmArgs& a, dim3 grid, hipStream_t stream) {
       return;
     }
   }
-  if (a.epi == ZO_EPI_RELU)
-    hipLaunchKernelGGL((k_gemm_main<F16, OUT, ZO_EPI_RELU>), grid, dim3(256), 0, stream, a);
-  else if (a.epi == ZO_EPI_RESIDUAL)
-    hipLaunchKernelGGL((k_gemm_main<F16, OUT, ZO_EPI_RESIDUAL>), grid, dim3(256), 0, stream, a);
-  else if (a.epi == ZO_EPI_SILU_MUL)
-    hipLaunchKernelGGL((k_gemm_main<F16, OUT, ZO_EPI_SILU_MUL>), grid, dim3(256), 0, stream, a);
+  if (a.K % 32 != 0)
+    launch_main_rag<F16, OUT, true>(a, grid, stream);
   else
-    hipLaunchKernelGGL((k_gemm_main<F16, OUT, ZO_EPI_NONE>), grid, dim3(256), 0, stream, a);
+    launch_main_rag<F16, OUT, false>(a, grid, stream);
 }
 
-// Whether k_gemm_main can take a call: K a multiple of 32 and every operand's buffer descriptor
-// span (rows x K, rows x rc elements of 2 bytes) below 2^32 bytes.
+// Whether k_gemm_main can take a call: K a multiple of 8 and every operand's buffer descriptor
+// span (rows x K, rows x rc elements of 2 bytes) below 2^32 bytes, 2^31 when K % 32 != 0.
 bool main_gemm_fits(const GemmArgs& a) {
-  const unsigned long long lim = (1ull << 32) - 256;
-  return a.K % 32 == 0 && (unsigned long long)a.rows_a * a.K * 2 <= lim &&
+  const unsigned long long lim = a.K % 32 ? 1ull << 31 : (1ull << 32) - 256;
+  return a.K % 8 == 0 && (unsigned long long)a.rows_a * a.K * 2 <= lim &&
          (unsigned long long)a.rows_b * a.K * 2 <= lim && (unsigned long long)a.rows_a * a.rc * 2 <= lim &&
          (unsigned long long)a.rows_b * a.rc * 2 <= lim;
 }
@@ -1762,7 +1779,7 @@ static bool proj_main_fits(const PlinearPlan& p, int count) {
   g.rows_b = p.T;
   g.K = p.n;
   return p.in16 && (p.rp == 32 || p.rp == 64) && count >= 1 && count <= ZO_MAX_GROUP && g.rows_a >= 128 &&
-         main_gemm_fits(g);
+         p.n % 32 == 0 && main_gemm_fits(g);
 }
 
 static int launch_proj_main(const PlinearPlan& p, const void* X, const void* vt, int count, bf16_t* const* pc,
