@@ -15,12 +15,10 @@
 // by each pass from L1/L2 (k_layernorm).  Both do the same operations in the
 // same order, so their results are identical.
 //
-// k_attention<F16, DH, W>: one workgroup (W = 4 or 8 waves) per (block, sequence,
-// head, tile of 32 W queries); keys in tiles of 64 through LDS (loaded into
-// registers a tile ahead, both K and V stored row-major), online softmax in
-// fp32.  Each wave owns AT_NG = 2 groups of 16 queries that share every K and
-// V fragment it reads from LDS (two groups measured 9-18 % faster than one once
-// the accumulators sit in VGPRs: 240 registers, two waves per SIMD), skips the
+// k_attention<F16, DH>: one workgroup of 4 waves per (block, sequence, head, tile
+// of 128 queries); keys in tiles of 64 through LDS (both K and V stored
+// row-major), online softmax in fp32.  Each wave owns AT_NG = 2 groups of 16
+// queries that share every K and V fragment it reads from LDS, skips the
 // tiles whose keys all follow its queries, and computes the transposed
 // products, which keeps every step in registers:
 //   S^T = K Q^T  (v_mfma_f32_16x16x32: A = K rows from LDS, B = the wave's Q
@@ -36,9 +34,19 @@
 //                 same assignment.
 // P enters as a hi + lo pair of 16-bit values (two MFMAs), so the product is
 // ~2^-16 accurate before the output's rounding; P is computed as
-// 2^((s - m) scale + 12) on the raw logits s (the common factor cancels in the
-// normalisation and keeps fp16 low parts out of the subnormal range), with the
-// running maximum m moved only when a logit exceeds it by more than 2^3.
+// 2^(s scale - m + 12) (the common factor cancels in the normalisation and keeps
+// fp16 low parts out of the subnormal range), with the running maximum m, a
+// whole number in log2 units, moved only when a logit exceeds it by more than 3.
+//
+// What bounds it: a wave's tile is a chain (S, maximum, exponentials, conversion, P V) of about 1500
+// matrix and 1600 vector cycles, and two or three waves per SIMD do not hide it.  So tile n + 1's S
+// MFMAs run under tile n's first exponentials and half of P V under the rest (K double buffered),
+// nothing but the last tile of a wave is masked, and 4-wave workgroups run out of step with
+// each other.  The workgroups of one K/V (query tiles, grouped heads) run on one XCD.
+// Before (8 waves in step, no overlap, K/V fetched per query tile) and now:
+//   OPT-13B layer, 16 x 8192 x 40 x 128, 512 keys: 2326 -> 2068 us (333 TFLOP/s of visible pairs)
+//   8 x 4096 x 32 x 128, 256 keys: 279 -> 262;  ... x 64: 155 -> 138
+//   fp16, 8 x 8192 x 20 x 64, 2048 keys: 1418 -> 700;  4 x 8192 x 20 (4 KV) x 128, 1024 keys: 526 -> 398
 #include "zo_internal.h"
 
 #include <type_traits>
@@ -255,9 +263,10 @@ __global__ __launch_bounds__(256) void k_rope(void* X, long long rows, int seq_l
 
 // ---------------------------------------------------------------- attention
 constexpr int AT_NG = 2;               // 16-query groups per wave
-// Waves per workgroup: 4, or 8 for sequences of 512 or more (the K/V tile a workgroup loads
-// then serves 256 queries; at 256 keys per sequence the causal tiles 8 waves would walk in
-// step cost more than that saves).
+// Waves per workgroup.  Four: two workgroups (three at 64 dims) per CU then run out of step, and one's
+// exponentials cover another's MFMAs and barriers.  Eight waves that share a K/V tile were 1 to 2.2
+// times slower (10 x 777 keys x 20 heads of 64, 12 blocks: 1010 against 521 us).
+constexpr int AT_W = 4;
 constexpr int AT_K = 64;               // keys per tile
 
 struct AttnArgs {
@@ -311,10 +320,19 @@ __device__ __forceinline__ u32x2 ds_read_tr(const uint16_t* p) {
   return __builtin_bit_cast(u32x2, v);
 }
 
-template <bool F16, int DH, int W>
-__global__ __launch_bounds__(64 * W) void k_attention(AttnArgs a) {
-  constexpr int NT = 64 * W;              // threads
-  constexpr int AT_Q = 16 * AT_NG * W;    // queries per workgroup
+// The maximum over the four 16-lane groups.
+__device__ __forceinline__ float max_groups(float x) {
+  const uint32_t u = __float_as_uint(x);
+  const auto a = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const uint32_t v = __float_as_uint(fmaxf(__uint_as_float(a[0]), __uint_as_float(a[1])));
+  const auto b = __builtin_amdgcn_permlane32_swap(v, v, false, false);
+  return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
+}
+
+template <bool F16, int DH>
+__global__ __launch_bounds__(64 * AT_W, DH == 64 ? 3 : 2) void k_attention(AttnArgs a) {
+  constexpr int W = AT_W, NT = 64 * W;  // waves, threads
+  constexpr int AT_Q = 16 * AT_NG * W;  // queries per workgroup
   constexpr int KS = DH / 32;         // 32-deep k steps of Q K^T
   constexpr int DT = DH / 16;         // 16-dim tiles of the output
   constexpr int KROW = DH + 8;        // LDS row of the K tile (elements), padded
@@ -323,11 +341,14 @@ __global__ __launch_bounds__(64 * W) void k_attention(AttnArgs a) {
   constexpr int C8 = DH / 8;          // 16-byte chunks per head row
   constexpr int KCH = AT_K * C8 / NT;    // K (and V) chunks per thread per tile
   static_assert(KCH * NT == AT_K * C8, "tile / thread mismatch");
-  __shared__ __attribute__((aligned(16))) uint16_t Ks[AT_K * KROW];
+  __shared__ __attribute__((aligned(16))) uint16_t Ks[2][AT_K * KROW];
   __shared__ __attribute__((aligned(16))) uint16_t Vs[AT_K * VROW];
 
-  // Workgroup -> (block, sequence, head, query tile).
-  int w = blockIdx.x;
+  // Workgroup -> (block, sequence, head, query tile).  The hardware deals workgroup w to XCD w % 8;
+  // each XCD gets a contiguous range, so the query tiles (and grouped query heads) that read the same
+  // K and V run on one XCD and share its L2.
+  int w = (int)(blockIdx.x & 7) * (int)(gridDim.x >> 3) + min((int)(blockIdx.x & 7), (int)(gridDim.x & 7)) +
+          (int)(blockIdx.x >> 3);
   const int qt = w % a.qtiles;
   w /= a.qtiles;
   const int head = w % a.heads;
@@ -364,62 +385,55 @@ __global__ __launch_bounds__(64 * W) void k_attention(AttnArgs a) {
   for (int gq = 0; gq < AT_NG; ++gq) {
 #pragma unroll
     for (int t = 0; t < DT; ++t) o[gq][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    mrow[gq] = -1e30f;  // running max of the raw logits
+    mrow[gq] = -1e30f;  // running maximum of the logits in log2 units, a whole number once set
     lsum[gq] = 0.f;     // this lane's part of the running sum
   }
 
-  // K and V tiles are loaded into registers a tile ahead: chunk x = tid + NT c is key x / C8,
-  // dims 8 (x % C8); both are stored row-major (V is read transposed by ds_read_tr).  Rows
-  // past the sequence are clamped to its last row (their keys are masked).
+  // K and V tiles go through registers: chunk x = tid + NT c is key x / C8, dims 8 (x % C8); both are
+  // stored row-major (V is read transposed by ds_read_tr).  Rows past the sequence are clamped to its
+  // last row (their keys are masked).
   u32x4 kreg[KCH], vreg[KCH];
-  auto load_tile = [&](int k0) {
+  auto load_tile = [&](const uint16_t* __restrict__ src, int k0, u32x4* reg) {
 #pragma unroll
     for (int c = 0; c < KCH; ++c) {
       const int x = tid + NT * c;
-      const size_t off = (size_t)(row0 + min(k0 + x / C8, a.seq_len - 1)) * a.dkv + col0kv + 8 * (x % C8);
-      kreg[c] = *(const u32x4*)(Kg + off);
-      vreg[c] = *(const u32x4*)(Vg + off);
+      reg[c] = *(const u32x4*)(src + (size_t)(row0 + min(k0 + x / C8, a.seq_len - 1)) * a.dkv + col0kv + 8 * (x % C8));
     }
   };
-  auto store_tile = [&]() {
+  auto store_tile = [&](uint16_t* dst, int pitch, const u32x4* reg) {
 #pragma unroll
     for (int c = 0; c < KCH; ++c) {
       const int x = tid + NT * c;
-      *(u32x4*)&Ks[(x / C8) * KROW + 8 * (x % C8)] = kreg[c];
-      *(u32x4*)&Vs[(x / C8) * VROW + 8 * (x % C8)] = vreg[c];
+      *(u32x4*)&dst[(x / C8) * pitch + 8 * (x % C8)] = reg[c];
     }
   };
 
-  const int kend = min(a.seq_len, q0 + AT_Q);  // keys beyond the tile's last query are never seen
-  load_tile(0);
-  for (int k0 = 0; k0 < kend; k0 += AT_K) {
-    __syncthreads();  // the previous tile has been consumed
-    store_tile();
-    __syncthreads();
-    if (k0 + AT_K < kend) load_tile(k0 + AT_K);
-    if (k0 > wq0 + 16 * AT_NG - 1) continue;  // every key of the tile is after the wave's queries
-
-    // S^T for 4 key subtiles of 16: st[gq][t][i] = key k0 + 16 t + 4 g + i, query myq[gq].
-    f32x4 st[AT_NG][4];
+  // S^T of key subtile t (16 keys) from a staged K tile: st[gq][t][i] = key 16 t + 4 g + i, query
+  // myq[gq].
+  auto qk = [&](const uint16_t* ks, int t, f32x4 (*st)[4]) {
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
+    for (int gq = 0; gq < AT_NG; ++gq) st[gq][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int gq = 0; gq < AT_NG; ++gq) st[gq][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
+    for (int kk = 0; kk < KS; ++kk) {
+      const bf16x8 kf = *(const bf16x8*)&ks[(16 * t + l16) * KROW + 32 * kk + 8 * g];
 #pragma unroll
-      for (int kk = 0; kk < KS; ++kk) {
-        const bf16x8 kf = *(const bf16x8*)&Ks[(16 * t + l16) * KROW + 32 * kk + 8 * g];
-#pragma unroll
-        for (int gq = 0; gq < AT_NG; ++gq) st[gq][t] = mfma16<F16>(kf, qf[gq][kk], st[gq][t]);
-      }
+      for (int gq = 0; gq < AT_NG; ++gq) st[gq][t] = mfma16<F16>(kf, qf[gq][kk], st[gq][t]);
     }
-    // Mask keys after the query (only a tile that reaches past the wave's first query has
-    // any), online softmax on the raw logits, P = 2^((s - m) scale + 12) as hi + lo 16-bit
-    // pairs in the B-operand order of the P V MFMA.  The running maximum m moves only when
-    // some query of the wave has a logit more than 3 (log2 units) above it, so most tiles
-    // skip the rescale of O; P then stays below 2^15 (within fp16's range), and the first
-    // tile sets m to its row maximum, whose P is exactly 2^12.
-    const bool diag = k0 + AT_K - 1 > wq0;
-    uint32_t ph[AT_NG][4][2], pl[AT_NG][4][2];
+  };
+  f32x4 sa[AT_NG][4];  // S^T of the tile at hand
+  // One tile of the wave: softmax and P V of st's tile.  NEXT: also the next tile's S^T (into sn, from
+  // kn).  Its MFMAs have no part in this tile's chain (maximum, exponentials, conversion, P V), so
+  // they run under the first half's exponentials, and the first half's P V under the second half's.
+  // A tile with a successor lies wholly before the wave's queries (both are multiples of 32); the
+  // last one is masked (MASK).
+  auto tile = [&](auto NEXT, int k0, const uint16_t* kn, f32x4 (*st)[4], f32x4 (*sn)[4]) {
+    constexpr bool next = decltype(NEXT)::value;
+    // Online softmax: P = 2^(s scale - m + 12) as hi + lo 16-bit pairs in the B-operand order of the
+    // P V MFMA.  m is a whole number, so 12 - m and the rescale factor 2^(m - m') are exact and each
+    // exponent is one fused multiply-add.  It moves only when some query of the wave has a logit
+    // more than 3 (log2 units) above it, so most tiles skip the rescale of O; P then stays at or
+    // below 2^15 (within fp16's range), and the first tile sets m to its row maximum rounded up.
+    float cadd[AT_NG];
 #pragma unroll
     for (int gq = 0; gq < AT_NG; ++gq) {
       float tmax = -1e30f;
@@ -427,45 +441,44 @@ __global__ __launch_bounds__(64 * W) void k_attention(AttnArgs a) {
       for (int t = 0; t < 4; ++t)
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-          if (diag && k0 + 16 * t + 4 * g + i > myq[gq]) st[gq][t][i] = -INFINITY;
+          if (!next && k0 + 16 * t + 4 * g + i > myq[gq]) st[gq][t][i] = -INFINITY;
           tmax = fmaxf(tmax, st[gq][t][i]);
         }
-      tmax = fmaxf(tmax, __shfl_xor(tmax, 16, 64));
-      tmax = fmaxf(tmax, __shfl_xor(tmax, 32, 64));
-      if (__ballot((tmax - mrow[gq]) * a.scale_log2 > 3.f)) {
-        const float mnew = fmaxf(mrow[gq], tmax);
-        const float alpha = __builtin_amdgcn_exp2f((mrow[gq] - mnew) * a.scale_log2);
+      tmax = max_groups(tmax);
+      if (__ballot(fmaf(tmax, a.scale_log2, -mrow[gq]) > 3.f)) {
+        const float mnew = fmaxf(mrow[gq], ceilf(tmax * a.scale_log2));
+        const float alpha = __builtin_amdgcn_exp2f(mrow[gq] - mnew);
         mrow[gq] = mnew;
         lsum[gq] *= alpha;
 #pragma unroll
         for (int t = 0; t < DT; ++t) o[gq][t] *= alpha;
       }
-      const float m = mrow[gq];
-#pragma unroll
-      for (int t = 0; t < 4; ++t)
-#pragma unroll
-        for (int i = 0; i < 4; i += 2) {
-          const float p0 = __builtin_amdgcn_exp2f(fmaf(st[gq][t][i] - m, a.scale_log2, 12.f));
-          const float p1 = __builtin_amdgcn_exp2f(fmaf(st[gq][t][i + 1] - m, a.scale_log2, 12.f));
-          lsum[gq] += p0 + p1;
-          const uint32_t h = cvt_pk<F16>(p0, p1);
-          ph[gq][t][i / 2] = h;
-          pl[gq][t][i / 2] = cvt_pk<F16>(p0 - unpk<F16>(h, 0), p1 - unpk<F16>(h, 1));
-        }
+      cadd[gq] = 12.f - mrow[gq];
     }
-    // O^T += V^T P^T over two 32-key chunks c (subtiles 2c and 2c+1): lane group g's k slots
-    // are keys 32c + 4g + (0..3) and 32c + 16 + 4g + (0..3); V^T's fragment (dim 16t + l16 of
-    // those keys) comes from two transposed reads of the row-major V tile.
-#pragma unroll
-    for (int c = 0; c < 2; ++c) {
-      bf16x8 bh[AT_NG], bl[AT_NG];
+    // P of 32-key chunk c (subtiles 2 c and 2 c + 1), as the two B operands per query group.
+    bf16x8 bh[2][AT_NG], bl[2][AT_NG];
+    auto probs = [&](int c) {
 #pragma unroll
       for (int gq = 0; gq < AT_NG; ++gq) {
-        bh[gq] = __builtin_bit_cast(bf16x8, (u32x4){ph[gq][2 * c][0], ph[gq][2 * c][1], ph[gq][2 * c + 1][0],
-                                                    ph[gq][2 * c + 1][1]});
-        bl[gq] = __builtin_bit_cast(bf16x8, (u32x4){pl[gq][2 * c][0], pl[gq][2 * c][1], pl[gq][2 * c + 1][0],
-                                                    pl[gq][2 * c + 1][1]});
+        u32x4 hp, lp;
+#pragma unroll
+        for (int x = 0; x < 4; ++x) {
+          const int t = 2 * c + (x >> 1), i = 2 * (x & 1);
+          const float p0 = __builtin_amdgcn_exp2f(fmaf(st[gq][t][i], a.scale_log2, cadd[gq]));
+          const float p1 = __builtin_amdgcn_exp2f(fmaf(st[gq][t][i + 1], a.scale_log2, cadd[gq]));
+          lsum[gq] += p0 + p1;
+          const uint32_t h = cvt_pk<F16>(p0, p1);
+          hp[x] = h;
+          lp[x] = cvt_pk<F16>(p0 - unpk<F16>(h, 0), p1 - unpk<F16>(h, 1));
+        }
+        bh[c][gq] = __builtin_bit_cast(bf16x8, hp);
+        bl[c][gq] = __builtin_bit_cast(bf16x8, lp);
       }
+    };
+    // O^T += V^T P^T over chunk c: lane group g's k slots are keys 32 c + 4 g + (0..3) and
+    // 32 c + 16 + 4 g + (0..3); V^T's fragment (dim 16 t + l16 of those keys) comes from two
+    // transposed reads of the row-major V tile.
+    auto pv = [&](int c) {
       const uint16_t* vb = &Vs[(32 * c + 4 * g + (l16 >> 2)) * VROW + 4 * (l16 & 3)];
 #pragma unroll
       for (int t = 0; t < DT; ++t) {
@@ -473,28 +486,94 @@ __global__ __launch_bounds__(64 * W) void k_attention(AttnArgs a) {
         const bf16x8 af = __builtin_bit_cast(bf16x8, (u32x4){v0[0], v0[1], v1[0], v1[1]});
 #pragma unroll
         for (int gq = 0; gq < AT_NG; ++gq) {
-          o[gq][t] = mfma16<F16>(af, bh[gq], o[gq][t]);
-          o[gq][t] = mfma16<F16>(af, bl[gq], o[gq][t]);
+          o[gq][t] = mfma16<F16>(af, bh[c][gq], o[gq][t]);
+          o[gq][t] = mfma16<F16>(af, bl[c][gq], o[gq][t]);
         }
       }
+    };
+    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (next) {
+#pragma unroll
+      for (int t = 0; t < 4; ++t) qk(kn, t, sn);
+    }
+    probs(0);
+    if constexpr (next) {
+#pragma unroll
+      for (int x = 0; x < 4 * KS; ++x) {
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);     // a K fragment
+        __builtin_amdgcn_sched_group_barrier(0x008, AT_NG, 0);  // its MFMAs
+        __builtin_amdgcn_sched_group_barrier(0x002, 8 * 4 / KS, 0);
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    pv(0);
+    probs(1);
+#pragma unroll
+    for (int x = 0; x < DT; ++x) {
+      __builtin_amdgcn_sched_group_barrier(0x100, 2, 1);         // a V fragment
+      __builtin_amdgcn_sched_group_barrier(0x008, 2 * AT_NG, 1);  // its MFMAs
+      __builtin_amdgcn_sched_group_barrier(0x002, 16 * 8 / DT, 1);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    pv(1);
+  };
+
+  const int kend = min(a.seq_len, q0 + AT_Q);  // keys beyond the tile's last query are never seen
+  load_tile(Kg, 0, kreg);
+  store_tile(Ks[0], KROW, kreg);
+  load_tile(Vg, 0, vreg);
+  if (AT_K < kend) load_tile(Kg, AT_K, kreg);
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < 4; ++t) qk(Ks[0], t, sa);
+  const int klast = min(wq0 + 16 * AT_NG, kend);  // the wave's tiles start below this
+  for (int k0 = 0, n = 0; k0 < kend; k0 += AT_K, ++n) {
+    // V(n) and K(n + 1) to LDS; K(n + 2) and V(n + 1) on their way.
+    uint16_t* const kn = Ks[(n + 1) & 1];
+    if (n) __syncthreads();  // tile n - 1 has been consumed
+    store_tile(Vs, VROW, vreg);
+    if (k0 + AT_K < kend) store_tile(kn, KROW, kreg);
+    __syncthreads();
+    if (k0 + AT_K < kend) load_tile(Vg, k0 + AT_K, vreg);
+    if (k0 + 2 * AT_K < kend) load_tile(Kg, k0 + 2 * AT_K, kreg);
+    if (k0 >= klast) continue;  // every key of the tile is after the wave's queries
+    if (k0 + AT_K < klast) {
+      f32x4 sn[AT_NG][4];
+      tile(std::true_type{}, k0, kn, sa, sn);
+#pragma unroll
+      for (int gq = 0; gq < AT_NG; ++gq)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) sa[gq][t] = sn[gq][t];
+    } else {
+      tile(std::false_type{}, k0, kn, sa, sa);
     }
   }
-  // Normalise by the row sums (over the 4 lane groups) and store dims 16 t + 4 g .. +3.
+  // Normalise by the row sums (over the 4 lane groups).  Rows go through LDS (the K buffers, no longer
+  // needed) so that a store covers whole 2 DH-byte rows instead of 16 pieces of 32 bytes.
+  __syncthreads();
+  uint16_t* const ow = Ks[0] + wave * 16 * AT_NG * KROW;
+  static_assert(16 * AT_NG * W * KROW <= 2 * AT_K * KROW, "the staged rows fit the K buffers");
 #pragma unroll
   for (int gq = 0; gq < AT_NG; ++gq) {
     float l = lsum[gq] + __shfl_xor(lsum[gq], 16, 64);
     l += __shfl_xor(l, 32, 64);
-    if (myq[gq] >= a.seq_len) continue;
     const float inv = 1.f / l;
-    uint16_t* op = (uint16_t*)a.O + (size_t)(row0 + myq[gq]) * a.d + col0 + 4 * g;
 #pragma unroll
     for (int t = 0; t < DT; ++t) {
       const float y0 = o[gq][t][0] * inv, y1 = o[gq][t][1] * inv;
       const float y2 = o[gq][t][2] * inv, y3 = o[gq][t][3] * inv;
       const u32x2 pk = F16 ? (u32x2){pack_f16x2(y0, y1), pack_f16x2(y2, y3)}
                            : (u32x2){pack_bf16x2(y0, y1), pack_bf16x2(y2, y3)};
-      *(u32x2*)(op + 16 * t) = pk;
+      *(u32x2*)&ow[(16 * gq + l16) * KROW + 16 * t + 4 * g] = pk;
     }
+  }
+  // Each wave reads back only its own rows.
+#pragma unroll
+  for (int x = lane; x < 16 * AT_NG * C8; x += 64) {
+    const int row = x / C8, c = x % C8;
+    const u32x4 v = *(const u32x4*)&ow[row * KROW + 8 * c];
+    if (wq0 + row < a.seq_len)
+      *(u32x4*)((uint16_t*)a.O + (size_t)(row0 + wq0 + row) * a.d + col0 + 8 * c) = v;
   }
 }
 
@@ -572,8 +651,7 @@ int zo_attention_launch(int nblk, int T, int seq_len, int d, int heads, int kv_h
   a.heads = heads;
   a.dkv = d / heads * kv_heads;
   a.group = heads / kv_heads;
-  const int W = seq_len >= 512 ? 8 : 4;
-  const int qpw = 16 * AT_NG * W;
+  const int qpw = 16 * AT_NG * AT_W;
   a.qtiles = (seq_len + qpw - 1) / qpw;
   const int dh = d / heads;
   a.scale_log2 = 1.4426950408889634f / sqrtf((float)dh);
@@ -583,21 +661,13 @@ int zo_attention_launch(int nblk, int T, int seq_len, int d, int heads, int kv_h
     zo_set_error("attention: too many workgroups (%lld)", wg);
     return ZO_ERR_UNSUPPORTED;
   }
-  const dim3 grid((unsigned)wg), block(64 * W);
+  const dim3 grid((unsigned)wg), block(64 * AT_W);
   const bool f16 = dtype == ZO_F16;
-#define ZO_ATTN(F, D, WW) hipLaunchKernelGGL((k_attention<F, D, WW>), grid, block, 0, stream, a)
-  if (W == 8) {
-    if (dh == 64) {
-      if (f16) ZO_ATTN(true, 64, 8); else ZO_ATTN(false, 64, 8);
-    } else {
-      if (f16) ZO_ATTN(true, 128, 8); else ZO_ATTN(false, 128, 8);
-    }
+#define ZO_ATTN(F, D) hipLaunchKernelGGL((k_attention<F, D>), grid, block, 0, stream, a)
+  if (dh == 64) {
+    if (f16) ZO_ATTN(true, 64); else ZO_ATTN(false, 64);
   } else {
-    if (dh == 64) {
-      if (f16) ZO_ATTN(true, 64, 4); else ZO_ATTN(false, 64, 4);
-    } else {
-      if (f16) ZO_ATTN(true, 128, 4); else ZO_ATTN(false, 128, 4);
-    }
+    if (f16) ZO_ATTN(true, 128); else ZO_ATTN(false, 128);
   }
 #undef ZO_ATTN
   return zo_hip_status(hipGetLastError(), "k_attention");
