@@ -3,19 +3,19 @@
 //   Y_b = X_b W^T + (X_b V) (s_b eps U Z_{j(b)})^T
 //
 // Launches per call (bf16 inputs):
-//   1. k_transpose_v : V (n x r fp32) -> Vt2 (2 rp x n bf16): rows [0, rp) the
+//   1. k_bprime      : V (n x r fp32) -> Vt2 (2 rp x n bf16): rows [0, rp) the
 //                      high bf16 part of V^T, rows [rp, 2 rp) the low part
 //                      (V = hi + lo to ~16 bits); rp = r rounded up to 32
-//                      (16 for fp32 inputs).
-//   2. k_bprime      : B_b = s_b eps U Z_{j(b)} (fp32) written as the K segment
+//                      (16 for fp32 inputs).  And, in other workgroups,
+//                      B_b = s_b eps U Z_{j(b)} (fp32) written as the K segment
 //                      [B_hi | B_lo | B_hi] (bf16, 3 rp wide), every block.
-//   3. projection    : P = X_x Vt2_hi^T + X_x Vt2_lo^T of every distinct X block,
+//   2. projection    : P = X_x Vt2_hi^T + X_x Vt2_lo^T of every distinct X block,
 //                      written as the K segment [P_hi | P_hi | P_lo] (bf16,
 //                      3 rp wide).  k_proj for one factor of 64 or 128 rows
 //                      (or two or three of 64), the main GEMM with the EPI_PROJ
 //                      epilogues for a wider stack of factors that read the same X;
 //                      otherwise an fp32 projection followed by k_pcombine.
-//   4. main GEMM     : Y_b = X_b W^T + P_{x(b)} B_b^T, the rank-r term added as
+//   3. main GEMM     : Y_b = X_b W^T + P_{x(b)} B_b^T, the rank-r term added as
 //                      one more 3 rp-deep K segment into the same fp32
 //                      accumulators: hi*hi + hi*lo + lo*hi, so the correction
 //                      carries ~2^-16 relative error instead of the 2^-8 of
@@ -399,20 +399,19 @@ __global__ __launch_bounds__(WM* WN * 64) void k_gemm_bf16(GemmArgs a) {
 
 // Vt[a][k] = V[k][a] for a < r, 0 for r <= a < rp.  16-bit: hi part in rows
 // [0, rp), low part (V - hi, rounded) in rows [rp, 2 rp); fp16 splits 256 V.
-// Factor blockIdx.y of a group that shares n, r and rp.
+// Factor f of a group that shares n, r and rp.
 struct TvArgs {
   const float* V[ZO_MAX_GROUP];
   void* Vt[ZO_MAX_GROUP];
   int n, r, rp, dtype;
 };
-__global__ __launch_bounds__(256) void k_transpose_v(TvArgs t) {
-  const long long idx = (long long)blockIdx.x * 256 + threadIdx.x;
+__device__ __forceinline__ void transpose_v(const TvArgs& t, int f, long long idx) {
   const int n = t.n, r = t.r, rp = t.rp;
   if (idx >= (long long)rp * n) return;
-  const float* __restrict__ V = t.V[blockIdx.y];
+  const float* __restrict__ V = t.V[f];
   const int a = (int)(idx / n), k = (int)(idx % n);
   const float v = a < r ? V[(size_t)k * r + a] : 0.f;
-  put_split(t.Vt[blockIdx.y], idx, (long long)rp * n, v, t.dtype);
+  put_split(t.Vt[f], idx, (long long)rp * n, v, t.dtype);
 }
 
 // P = (P2[:, :rp] + P2[:, rp:]) * unscale (fp32; unscale a power of two; P2 rows ld2 apart),
@@ -454,8 +453,10 @@ struct BpShape {
   static constexpr int R = RR * RT;   // rows per workgroup
 };
 
-// Factor blockIdx.z of a group that shares r, rp, the blocks and eps (one factor: a group of 1);
-// the grid covers the tallest factor.
+// One launch for both prepared factors of a group that shares r, rp, the blocks and eps (one
+// factor: a group of 1): workgroups 0 .. nb - 1 form B' (row tile fastest, then query, then factor;
+// the row tiles cover the tallest factor), the rest V^T.  Neither reads the other, and each is a few
+// microseconds.
 struct BpArgs {
   const float* U[ZO_MAX_GROUP];
   const float* Z[ZO_MAX_GROUP];
@@ -463,6 +464,8 @@ struct BpArgs {
   int m[ZO_MAX_GROUP];
   int r, rp, nblk, out_bf16;
   float eps;
+  int q, tiles, nb, tv;  // queries, row tiles, B' workgroups, V^T workgroups per factor
+  TvArgs t;
   BlkTable tab;
 };
 
@@ -473,14 +476,19 @@ __global__ __launch_bounds__(256) void k_bprime(BpArgs a) {
   constexpr int UL = RP + 4;  // floats per staged U row (rows 4 banks apart)
   __shared__ __attribute__((aligned(16))) float Zl[32 * RP];  // 32 rows of Z_j at a time
   __shared__ __attribute__((aligned(16))) float Ul[R * UL];
-  const int f = blockIdx.z;
+  if ((int)blockIdx.x >= a.nb) {
+    const int w = blockIdx.x - a.nb;
+    transpose_v(a.t, w / a.tv, (long long)(w % a.tv) * 256 + threadIdx.x);
+    return;
+  }
+  const int f = blockIdx.x / (a.tiles * a.q);
   const int m = a.m[f], r = a.r, rp = a.rp, nblk = a.nblk, out_bf16 = a.out_bf16;
   const float eps = a.eps;
   const float* __restrict__ U = a.U[f];
   const float* __restrict__ Z = a.Z[f];
   void* const Bp = a.Bp[f];
-  const int j = blockIdx.y;
-  const int i0 = blockIdx.x * R;
+  const int j = blockIdx.x / a.tiles % a.q;
+  const int i0 = (int)(blockIdx.x % a.tiles) * R;
   if (i0 >= m) return;  // past a shorter factor: the whole workgroup, before any barrier
   const int tid = threadIdx.x;
   const float* __restrict__ Zj = Z + (size_t)j * r * r;
@@ -1671,28 +1679,11 @@ PlinearWs zo_plinear_ws(const PlinearPlan& p, void* ws) {
   return w;
 }
 
-// Vt2 of `count` factors that share n, r and rp (plans[i] gives factor i's; V[i] -> vt[i]).
-static int launch_transpose_v(const PlinearPlan* plans, int count, const float* const* V, void* const* vt,
-                              hipStream_t stream) {
-  const PlinearPlan& p = plans[0];
-  TvArgs t{};
-  for (int i = 0; i < count; ++i) {
-    t.V[i] = V[i];
-    t.Vt[i] = vt[i];
-  }
-  t.n = p.n;
-  t.r = p.r;
-  t.rp = p.rp;
-  t.dtype = p.in_dtype;
-  const long long total = (long long)p.rp * p.n;
-  hipLaunchKernelGGL(k_transpose_v, dim3((unsigned)((total + 255) / 256), (unsigned)count), dim3(256), 0, stream,
-                     t);
-  return zo_hip_status(hipGetLastError(), "k_transpose_v");
-}
-
-// B' of `count` factors that share r, rp, the blocks and eps (heights may differ): one launch.
-static int launch_bprime(const PlinearPlan* plans, int count, const BlkTable& tab, float eps,
-                         const float* const* U, const float* const* Z, void* const* bp, hipStream_t stream) {
+// B' and Vt2 of `count` factors that share n, r, rp, the blocks and eps (heights may differ;
+// plans[i] gives factor i's): one launch.
+static int launch_factors(const PlinearPlan* plans, int count, const BlkTable& tab, float eps,
+                          const float* const* U, const float* const* V, const float* const* Z, void* const* bp,
+                          void* const* vt, hipStream_t stream) {
   const PlinearPlan& p = plans[0];
   BpArgs a{};
   int mmax = 0;
@@ -1701,6 +1692,8 @@ static int launch_bprime(const PlinearPlan* plans, int count, const BlkTable& ta
     a.Z[i] = Z[i];
     a.Bp[i] = bp[i];
     a.m[i] = plans[i].m;
+    a.t.V[i] = V[i];
+    a.t.Vt[i] = vt[i];
     mmax = std::max(mmax, plans[i].m);
   }
   a.r = p.r;
@@ -1708,13 +1701,28 @@ static int launch_bprime(const PlinearPlan* plans, int count, const BlkTable& ta
   a.nblk = p.nblk;
   a.out_bf16 = p.in16;
   a.eps = eps;
+  a.q = p.q;
   a.tab = tab;
-  auto grid = [&](int rows) { return dim3((unsigned)((mmax + rows - 1) / rows), (unsigned)p.q, (unsigned)count); };
-  switch ((p.r + 31) / 32) {
-    case 1: hipLaunchKernelGGL(k_bprime<1>, grid(BpShape<1>::R), dim3(256), 0, stream, a); break;
-    case 2: hipLaunchKernelGGL(k_bprime<2>, grid(BpShape<2>::R), dim3(256), 0, stream, a); break;
-    case 3: hipLaunchKernelGGL(k_bprime<3>, grid(BpShape<3>::R), dim3(256), 0, stream, a); break;
-    default: hipLaunchKernelGGL(k_bprime<4>, grid(BpShape<4>::R), dim3(256), 0, stream, a); break;
+  a.t.n = p.n;
+  a.t.r = p.r;
+  a.t.rp = p.rp;
+  a.t.dtype = p.in_dtype;
+  const int rpk = (p.r + 31) / 32;
+  const int rows = rpk == 1 ? BpShape<1>::R : rpk == 2 ? BpShape<2>::R : rpk == 3 ? BpShape<3>::R : BpShape<4>::R;
+  a.tiles = (mmax + rows - 1) / rows;
+  const long long nb = (long long)a.tiles * p.q * count, tv = ((long long)p.rp * p.n + 255) / 256;
+  if (nb + tv * count > 0x7fffffffLL) {
+    zo_set_error("perturbed linear: too many workgroups in the prepare (%lld)", nb + tv * count);
+    return ZO_ERR_UNSUPPORTED;
+  }
+  a.nb = (int)nb;
+  a.tv = (int)tv;
+  const dim3 grid((unsigned)(nb + tv * count));
+  switch (rpk) {
+    case 1: hipLaunchKernelGGL(k_bprime<1>, grid, dim3(256), 0, stream, a); break;
+    case 2: hipLaunchKernelGGL(k_bprime<2>, grid, dim3(256), 0, stream, a); break;
+    case 3: hipLaunchKernelGGL(k_bprime<3>, grid, dim3(256), 0, stream, a); break;
+    default: hipLaunchKernelGGL(k_bprime<4>, grid, dim3(256), 0, stream, a); break;
   }
   return zo_hip_status(hipGetLastError(), "k_bprime");
 }
@@ -1726,8 +1734,8 @@ int zo_plinear_prepare(const PlinearPlan& p, const int* blk_query, const int8_t*
   int st;
   void* vt = w.vt;
   void* bp = w.bp;
-  if ((st = launch_transpose_v(&p, 1, &V, &vt, stream)) != ZO_OK) return st;
-  if ((st = launch_bprime(&p, 1, zo_blk_table(p.nblk, blk_query, blk_sign), eps, &U, &Z, &bp, stream)) != ZO_OK)
+  if ((st = launch_factors(&p, 1, zo_blk_table(p.nblk, blk_query, blk_sign), eps, &U, &V, &Z, &bp, &vt, stream)) !=
+      ZO_OK)
     return st;
   return zo_plinear_project(p, X, ws, stream);
 }
@@ -1850,15 +1858,14 @@ int zo_plinear_prepare_group(const PlinearPlan* plans, int count, const int* blk
   char* gvt = (char*)gws;
   float* gp2 = (float*)(gvt + zo_align256((size_t)count * w2 * p0.n * 2));
   const BlkTable tab = zo_blk_table(p0.nblk, blk_query, blk_sign);
-  // Vt2 and B' of every factor of the group: one launch each.
+  // Vt2 and B' of every factor of the group.
   void* vts[ZO_MAX_GROUP];
   void* bps[ZO_MAX_GROUP];
   for (int i = 0; i < count; ++i) {
     vts[i] = gvt + (size_t)i * w2 * p0.n * 2;
     bps[i] = zo_plinear_ws(plans[i], ws[i]).bp;
   }
-  if ((st = launch_transpose_v(plans, count, V, vts, stream)) != ZO_OK) return st;
-  if ((st = launch_bprime(plans, count, tab, eps, U, Z, bps, stream)) != ZO_OK) return st;
+  if ((st = launch_factors(plans, count, tab, eps, U, V, Z, bps, vts, stream)) != ZO_OK) return st;
   // Up to 128 rows in all go to k_proj, and three factors of 64 rows while its 256-token tiles
   // would not fill the chip; other stacks stay on the main GEMM's 256-row tiles (two factors of 128
   // rows per X tile: the stacked q, k, v run 0.50 ms there against 0.72 ms in three 128-row tiles of

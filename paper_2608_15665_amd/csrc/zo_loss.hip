@@ -51,8 +51,8 @@ __device__ __forceinline__ double sq_chunk(const void* Y, const void* Ystar, lon
 }
 
 __global__ __launch_bounds__(256) void k_sq_partial(const void* Y, const void* Ystar, int dtype,
-                                                    long long per_block, int nchunk, int vec,
-                                                    double* partial) {
+                                                    long long per_block, int nchunk, int vec, int T,
+                                                    double* partial, double* out) {
   __shared__ double red[4];
   const int c = blockIdx.x, b = blockIdx.y;
   const long long lo = (long long)c * LOSS_CHUNK;
@@ -68,7 +68,11 @@ __global__ __launch_bounds__(256) void k_sq_partial(const void* Y, const void* Y
   for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
   if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
   __syncthreads();
-  if (threadIdx.x == 0) partial[(long long)b * nchunk + c] = (red[0] + red[1]) + (red[2] + red[3]);
+  if (threadIdx.x == 0) {
+    const double sum = (red[0] + red[1]) + (red[2] + red[3]);
+    if (nchunk == 1) out[b] = 0.5 * sum / (double)T;  // a block of one chunk needs no second launch
+    else partial[(long long)b * nchunk + c] = sum;
+  }
 }
 
 // One wave per block: lane l sums the chunk partials l, l + 64, ... in order, then the lanes
@@ -113,9 +117,9 @@ int zo_sq_loss_launch(int nblk, int T, int m, int dtype, const void* Y, const vo
   const int esz = dtype == ZO_F32 ? 4 : 2;
   const int vec = (per * esz) % 16 == 0 && (uintptr_t)Y % 16 == 0 && (uintptr_t)Ystar % 16 == 0;
   hipLaunchKernelGGL(k_sq_partial, dim3(nchunk, nblk), dim3(256), 0, stream, Y, Ystar,
-                     dtype, per, nchunk, vec, partial);
+                     dtype, per, nchunk, vec, T, partial, out);
   int st = zo_hip_status(hipGetLastError(), "k_sq_partial");
-  if (st != ZO_OK) return st;
+  if (st != ZO_OK || nchunk == 1) return st;
   hipLaunchKernelGGL(k_sq_final, dim3(nblk), dim3(64), 0, stream, partial, nchunk, nblk, T, out);
   return zo_hip_status(hipGetLastError(), "k_sq_final");
 }
