@@ -27,7 +27,7 @@
 // against 2 r MACs.  At r = 64 that is 32 FLOP/B, above the fp32 VALU ridge
 // of the chip, so the rank-r product runs on v_mfma_f32_16x16x32_bf16 as
 // hi*hi + lo*hi + hi*lo (3 MFMAs per 32-deep K step).  Each wave owns a strip
-// of 64 columns whose V fragments stay in registers and walks its rows 16 at a
+// of 128 columns (64 for r > 64) whose V fragments stay in registers and walks its rows 16 at a
 // time; the L rows are staged once per workgroup in LDS.
 //
 // Every W, L and V access of k_update_bf16 is a buffer instruction whose
@@ -36,6 +36,7 @@
 // stores in hardware, so the loop has no branches around memory operations
 // and the compiler can count the loads in flight exactly.  W is read NS steps
 // ahead and the next L chunk one chunk ahead.
+#include <type_traits>
 #include <vector>
 
 #include "zo_internal.h"
@@ -44,8 +45,14 @@ namespace {
 
 constexpr int FILL_ITEMS = 16;           // descriptors per k_fill_items launch
 constexpr long long MAX_PASS_WG = 1 << 22; // workgroups per launch (x 256 threads < 2^32)
-constexpr int UPD_ROWS = 512;  // rows per workgroup
-constexpr int UPD_COLS = 256;  // columns per workgroup (4 waves x 64)
+// Adjacent columns per lane: 16 bytes of W each way where the V fragments of 128 columns per wave fit
+// the registers (r <= 64), else 8.
+constexpr int upd_cpl(int rpk) { return rpk <= 2 ? 8 : 4; }
+constexpr int upd_cols(int rpk) { return 64 * upd_cpl(rpk); }  // columns per workgroup (4 waves)
+// Rows per workgroup: the wide strips take half the rows, so that a call has as many workgroups.
+// Whole call, us, 8-byte pieces x 512 rows / 16-byte x 512 / 16-byte x 256: r = 64, d = 5120: 324 / 308 /
+// 313; r = 32, d = 4096: 140 / 145 / 135; r = 16, d = 2048: 54 / 51 / 52; r = 64, d = 384: 49 / 51 / 47.
+constexpr int upd_rows(int rpk) { return rpk <= 2 ? 256 : 512; }
 constexpr int UPD_GROUP = 4;   // row chunks per raster group
 constexpr int US_ROWS = 128;   // rows of L per k_us workgroup
 constexpr unsigned OOB = 0x80000000u;  // buffer offset beyond every descriptor used here
@@ -298,27 +305,32 @@ __device__ __forceinline__ void bstore(__amdgpu_buffer_rsrc_t r, unsigned off, u
   __builtin_amdgcn_raw_buffer_store_b128(v, r, (int)off, 0, 0);
 }
 
-__device__ __forceinline__ u32x2 bload2(__amdgpu_buffer_rsrc_t r, unsigned off) {
-  return __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0);
+// A lane's W columns of one row: 16 or 8 bytes.
+__device__ __forceinline__ void bload_piece(__amdgpu_buffer_rsrc_t r, unsigned off, u32x4& v) { v = bload(r, off); }
+__device__ __forceinline__ void bload_piece(__amdgpu_buffer_rsrc_t r, unsigned off, u32x2& v) {
+  v = __builtin_amdgcn_raw_buffer_load_b64(r, (int)off, 0, 0);
 }
-__device__ __forceinline__ void bstore2(__amdgpu_buffer_rsrc_t r, unsigned off, u32x2 v) {
+__device__ __forceinline__ void bstore_piece(__amdgpu_buffer_rsrc_t r, unsigned off, u32x4 v) { bstore(r, off, v); }
+__device__ __forceinline__ void bstore_piece(__amdgpu_buffer_rsrc_t r, unsigned off, u32x2 v) {
   __builtin_amdgcn_raw_buffer_store_b64(v, r, (int)off, 0, 0);
 }
 
-// Workgroup tile: UPD_ROWS rows x 256 columns (4 waves x 64 columns), walked in
+// Workgroup tile: upd_rows x upd_cols (4 waves x 16 CPL columns), walked in
 // chunks of CH = 16 NS rows.  Per chunk: the chunk's L rows (loaded a chunk
 // earlier into registers) go to LDS, the next chunk's L is requested, and each
 // of the NS steps multiplies 16 rows, stores them and requests the same step of
 // the next chunk.  The MFMA takes L rows as its A operand and V columns as its
-// B operand, column j of tile t being W column 4 j + t of the wave's strip: a
-// lane ends with 4 ADJACENT columns of rows 4 g .. 4 g + 3 (g = lane / 16),
-// so each memory instruction of a wave covers 4 rows x 128 contiguous bytes --
-// whole cache lines.  The prologue issues range-dropped stores in place of each
+// B operand, column j of tile t being W column CPL j + t of the wave's strip: a
+// lane ends with CPL ADJACENT columns of rows 4 g .. 4 g + 3 (g = lane / 16),
+// so each memory instruction of a wave covers 4 rows x 32 CPL contiguous bytes --
+// whole cache lines, and twice the bytes in flight at CPL = 8.  The prologue
+// issues range-dropped stores in place of each
 // step's stores so that the count of memory operations between a load and its
 // use is the same on entry as in the steady state.
 template <int RPK, bool HOOK, bool WF16>
 __global__ __launch_bounds__(256) void k_update_bf16(UpdArgs a) {
   constexpr int RP = 32 * RPK;
+  constexpr int CPL = upd_cpl(RPK), UPD_ROWS = upd_rows(RPK);
   constexpr int NS = RPK == 1 ? 4 : 2;  // W prefetch depth in 16-row steps
   constexpr int CH = 16 * NS;           // rows per L chunk
   constexpr int LROW = RP * 4 + 16;     // bytes per staged L row [hi | lo] (+16: conflict-free reads)
@@ -349,7 +361,7 @@ __global__ __launch_bounds__(256) void k_update_bf16(UpdArgs a) {
   const int wave = tid >> 6;
   const int l16 = lane & 15, g = lane >> 4;
   const int m = it.m, n = it.n;
-  const int col0 = strip * UPD_COLS + wave * 64;
+  const int col0 = strip * upd_cols(RPK) + wave * 16 * CPL;
   const int row0 = rchunk * UPD_ROWS;
   const int rows = min(UPD_ROWS, m - row0);
   const int nch = (rows + CH - 1) / CH;
@@ -364,11 +376,11 @@ __global__ __launch_bounds__(256) void k_update_bf16(UpdArgs a) {
   if (HOOK) ro = it.wout ? rsrc(it.wout + (size_t)row0 * n, (unsigned)rows * n * 4) : rsrc(Wt, 0u);
 
   // V fragments of the strip (B operand): column j = l16 of tile t is W column
-  // col0 + 4 j + t.
-  const int cb = col0 + 4 * l16;
-  bf16x8 vh[RPK][4], vl[RPK][4];
+  // col0 + CPL j + t.
+  const int cb = col0 + CPL * l16;
+  bf16x8 vh[RPK][CPL], vl[RPK][CPL];
 #pragma unroll
-  for (int t = 0; t < 4; ++t) {
+  for (int t = 0; t < CPL; ++t) {
 #pragma unroll
     for (int kk = 0; kk < RPK; ++kk) {
       const bool ok = cb + t < n;
@@ -381,8 +393,8 @@ __global__ __launch_bounds__(256) void k_update_bf16(UpdArgs a) {
   // otherwise count them as possibly in flight on every iteration.
   __builtin_amdgcn_s_waitcnt(0x0f70);  // vmcnt(0)
 
-  // This lane's W pieces: rows 4 g + v (v = 0..3) of each step, columns cb .. cb+3
-  // (n % 8 == 0, so the 4 columns are all in range or all out).
+  // This lane's W pieces: rows 4 g + v (v = 0..3) of each step, columns cb .. cb + CPL - 1
+  // (n % 8 == 0, so they are all in range or all out).
   const unsigned stepw = (unsigned)(16 * n * 2);
   unsigned wo[4], ho[4];
 #pragma unroll
@@ -404,20 +416,21 @@ __global__ __launch_bounds__(256) void k_update_bf16(UpdArgs a) {
   const unsigned chunk_l = (unsigned)(CH * RP * 4);
 
   u32x4 lreg[NL];
-  u32x2 wb[NS][4];
+  using Piece = typename std::conditional<CPL == 8, u32x4, u32x2>::type;
+  Piece wb[NS][4];
 #pragma unroll
   for (int x = 0; x < NL; ++x) lreg[x] = bload(rl, lo_g[x]);
 #pragma unroll
   for (int s = 0; s < NS; ++s) {
     // Distinct offsets keep the compiler from merging the dropped stores.
 #pragma unroll
-    for (int v = 0; v < 4; ++v) bstore2(rw, OOB + 32 * s + 8 * v, (u32x2){0u, 0u});
+    for (int v = 0; v < 4; ++v) bstore_piece(rw, OOB + 64 * s + 16 * v, Piece{});
     if (HOOK) {
 #pragma unroll
-      for (int v = 0; v < 4; ++v) bstore(ro, OOB + 64 * s + 16 * v, (u32x4){0u, 0u, 0u, 0u});
+      for (int v = 0; v < CPL; ++v) bstore(ro, OOB + 128 * s + 16 * v, (u32x4){0u, 0u, 0u, 0u});
     }
 #pragma unroll
-    for (int v = 0; v < 4; ++v) wb[s][v] = bload2(rw, wo[v] + s * stepw);
+    for (int v = 0; v < 4; ++v) bload_piece(rw, wo[v] + s * stepw, wb[s][v]);
   }
 
   for (int c = 0; c < nch; ++c) {
@@ -436,9 +449,9 @@ __global__ __launch_bounds__(256) void k_update_bf16(UpdArgs a) {
         uh[kk] = *(const bf16x8*)lp;
         ul[kk] = *(const bf16x8*)(lp + RP * 2);
       }
-      f32x4 acc[4];
+      f32x4 acc[CPL];
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
+      for (int t = 0; t < CPL; ++t) {
         acc[t] = (f32x4){0.f, 0.f, 0.f, 0.f};
 #pragma unroll
         for (int kk = 0; kk < RPK; ++kk) {
@@ -451,26 +464,31 @@ __global__ __launch_bounds__(256) void k_update_bf16(UpdArgs a) {
       const unsigned d = (unsigned)(c * NS + s) * stepw;
 #pragma unroll
       for (int v = 0; v < 4; ++v) {
-        const uint32_t w0 = wb[s][v][0], w1 = wb[s][v][1];
-        float n0, n1, n2, n3;
-        if constexpr (WF16) {
-          n0 = f16_to_f32((uint16_t)w0) - acc[0][v];
-          n1 = f16_to_f32((uint16_t)(w0 >> 16)) - acc[1][v];
-          n2 = f16_to_f32((uint16_t)w1) - acc[2][v];
-          n3 = f16_to_f32((uint16_t)(w1 >> 16)) - acc[3][v];
-          bstore2(rw, wo[v] + d, (u32x2){pack_f16x2(n0, n1), pack_f16x2(n2, n3)});
-        } else {
-          n0 = __uint_as_float(w0 << 16) - acc[0][v];
-          n1 = __uint_as_float(w0 & 0xffff0000u) - acc[1][v];
-          n2 = __uint_as_float(w1 << 16) - acc[2][v];
-          n3 = __uint_as_float(w1 & 0xffff0000u) - acc[3][v];
-          bstore2(rw, wo[v] + d, (u32x2){pack_bf16x2(n0, n1), pack_bf16x2(n2, n3)});
+        Piece o;
+        float nv[CPL];
+#pragma unroll
+        for (int x = 0; x < CPL / 2; ++x) {
+          const uint32_t w = wb[s][v][x];
+          if constexpr (WF16) {
+            nv[2 * x] = f16_to_f32((uint16_t)w) - acc[2 * x][v];
+            nv[2 * x + 1] = f16_to_f32((uint16_t)(w >> 16)) - acc[2 * x + 1][v];
+            o[x] = pack_f16x2(nv[2 * x], nv[2 * x + 1]);
+          } else {
+            nv[2 * x] = __uint_as_float(w << 16) - acc[2 * x][v];
+            nv[2 * x + 1] = __uint_as_float(w & 0xffff0000u) - acc[2 * x + 1][v];
+            o[x] = pack_bf16x2(nv[2 * x], nv[2 * x + 1]);
+          }
         }
-        if (HOOK) bstore(ro, ho[v] + 2 * d, __builtin_bit_cast(u32x4, (f32x4){n0, n1, n2, n3}));
+        bstore_piece(rw, wo[v] + d, o);
+        if (HOOK) {
+#pragma unroll
+          for (int x = 0; x < CPL; x += 4)
+            bstore(ro, ho[v] + 2 * d + 4 * x, __builtin_bit_cast(u32x4, (f32x4){nv[x], nv[x + 1], nv[x + 2], nv[x + 3]}));
+        }
       }
       const unsigned dn = (unsigned)((c + 1) * NS + s) * stepw;
 #pragma unroll
-      for (int v = 0; v < 4; ++v) wb[s][v] = bload2(rw, wo[v] + dn);
+      for (int v = 0; v < 4; ++v) bload_piece(rw, wo[v] + dn, wb[s][v]);
     }
   }
 }
@@ -584,8 +602,9 @@ int zo_update_launch(int count, const zo_update_item* items, int w_dtype, int r,
     us_total += it.us_wg;
     it.up_begin = (int)up_total;
     if (bf16) {
-      it.strips = (src.n + UPD_COLS - 1) / UPD_COLS;
-      it.rchunks = (src.m + UPD_ROWS - 1) / UPD_ROWS;
+      const int cols = upd_cols(rp / 32);
+      it.strips = (src.n + cols - 1) / cols;
+      it.rchunks = (src.m + upd_rows(rp / 32) - 1) / upd_rows(rp / 32);
       up_total += (long long)it.strips * it.rchunks;
     } else {
       it.strips = it.rchunks = 1;
