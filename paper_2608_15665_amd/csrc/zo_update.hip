@@ -14,8 +14,7 @@
 //               to zbar_out.
 //   k_us        Reads the item's flags: if any entry was non-finite the item is
 //               skipped (state untouched).  Otherwise commits the new moments and
-//               forms L = lr U S (m x rp; tiles of 128 rows, register-blocked fp32
-//               FMA) and, for 16-bit W, the hi/lo split of V (n x rp); padding
+//               forms L = lr U S (m x rp; tiles of 64 rows, fp32 MFMA) and, for 16-bit W, the hi/lo split of V (n x rp); padding
 //               columns are zero.  16-bit W: L and V as hi + lo bf16 pairs (x = hi +
 //               lo to about 16 significant bits, with fp32's range); fp32 W: L in
 //               fp32, V read as is.
@@ -54,7 +53,7 @@ constexpr int upd_cols(int rpk) { return 64 * upd_cpl(rpk); }  // columns per wo
 // 313; r = 32, d = 4096: 140 / 145 / 135; r = 16, d = 2048: 54 / 51 / 52; r = 64, d = 384: 49 / 51 / 47.
 constexpr int upd_rows(int rpk) { return rpk <= 2 ? 256 : 512; }
 constexpr int UPD_GROUP = 4;   // row chunks per raster group
-constexpr int US_ROWS = 128;   // rows of L per k_us workgroup
+constexpr int US_ROWS = 64;    // rows of L per k_us workgroup (16 per wave)
 constexpr unsigned OOB = 0x80000000u;  // buffer offset beyond every descriptor used here
 constexpr int RSRC_CFG = 0x00020000;   // buffer descriptor word 3: 32-bit raw access
 
@@ -170,15 +169,20 @@ struct USArgs {
   float lr;
 };
 
-// L = lr U S for rows i0 .. i0+127 of one item: 32 columns of K at a time, U
-// (transposed) and S staged in LDS as fp32; each thread owns 4 rows x rp/8
-// adjacent columns.  Or the hi/lo split of 64 rows of V.
+typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+
+// L = lr U S for US_ROWS rows of one item, on v_mfma_f32_16x16x4_f32 (fp32 products and sums):
+// S is staged in LDS as fp32, transposed, and each wave multiplies 16 of its rows of U, read 16 bytes
+// per lane straight from memory, by all of it.  A 16-byte piece feeds four MFMAs (element e of
+// every lane in MFMA e: k = 4 g + e of a 16-deep slice, the same for both operands).  S^T is
+// the A operand, so a lane ends with 4 adjacent columns of one row.  Or the hi/lo split of 64 rows of
+// V.  (On the vector FMA, 128 rows per workgroup and U staged a float at a time: 43 us for an
+// OPT-13B layer's six matrices at r = 64, against 24.)
 template <int RPK>
 __global__ __launch_bounds__(256) void k_us(USArgs a) {
   constexpr int RP = 32 * RPK;
-  constexpr int CPT = RP / 8;  // columns per thread
-  __shared__ __attribute__((aligned(16))) float Ut[32][US_ROWS + 4];
-  __shared__ __attribute__((aligned(16))) float Sl[32][RP];
+  constexpr int SP = RP + 4;  // pitch of S^T's rows: 16 of them at one 16-byte column on distinct banks
+  __shared__ __attribute__((aligned(16))) float St[RP * SP];
   const int b = a.wg0 + (int)blockIdx.x;
   const Item it = a.it[find_item(a.begin, a.count, b)];
   const int local = b - it.us_begin;
@@ -196,66 +200,54 @@ __global__ __launch_bounds__(256) void k_us(USArgs a) {
     }
   }
   if (local < it.l_tiles) {
-    const int i0 = local * US_ROWS;
-    const int tr = tid >> 3, tc = tid & 7;
-    float acc[4][CPT];
+    for (int x = tid; x < RP * RP; x += 256) {
+      const int t = x / RP, c = x % RP;
+      St[c * SP + t] = (t < r && c < r) ? (float)it.S[t * r + c] : 0.f;
+    }
+    __syncthreads();
+    const int lane = tid & 63, l16 = lane & 15, g = lane >> 4;
+    const int row = local * US_ROWS + (tid >> 6) * 16 + l16;
+    const float* u = it.U + (size_t)min(row, it.m - 1) * r;
+    f32x4 uf[RP / 16];
 #pragma unroll
-    for (int x = 0; x < 4; ++x)
+    for (int k = 0; k < RP / 16; ++k) {
+      const int c = 16 * k + 4 * g;
+      uf[k] = (f32x4){0.f, 0.f, 0.f, 0.f};
+      if (c + 4 <= r) {
+        uf[k] = (f32x4)*(const f32x4_a4*)(u + c);
+      } else {
 #pragma unroll
-      for (int y = 0; y < CPT; ++y) acc[x][y] = 0.f;
-    for (int kc = 0; kc < RPK; ++kc) {
-      if (kc) __syncthreads();
-      for (int x = tid; x < 32 * US_ROWS; x += 256) {
-        const int i = x >> 5, kk = x & 31, t = kc * 32 + kk;
-        Ut[kk][i] = (i0 + i < it.m && t < r) ? it.U[(size_t)(i0 + i) * r + t] : 0.f;
-      }
-      for (int x = tid; x < 32 * RP; x += 256) {
-        const int kk = x / RP, c = x % RP, t = kc * 32 + kk;
-        Sl[kk][c] = (t < r && c < r) ? (float)it.S[t * r + c] : 0.f;
-      }
-      __syncthreads();
-#pragma unroll 4
-      for (int kk = 0; kk < 32; ++kk) {
-        const f32x4 u = *(const f32x4*)&Ut[kk][tr * 4];
-        float s[CPT];
-#pragma unroll
-        for (int y = 0; y < CPT; y += 4) {
-          const f32x4 sv = *(const f32x4*)&Sl[kk][tc * CPT + y];
-          s[y] = sv[0];
-          s[y + 1] = sv[1];
-          s[y + 2] = sv[2];
-          s[y + 3] = sv[3];
-        }
-#pragma unroll
-        for (int x = 0; x < 4; ++x)
-#pragma unroll
-          for (int y = 0; y < CPT; ++y) acc[x][y] = fmaf(u[x], s[y], acc[x][y]);
+        for (int e = 0; e < 3; ++e)
+          if (c + e < r) uf[k][e] = u[c + e];
       }
     }
 #pragma unroll
-    for (int x = 0; x < 4; ++x) {
-      const int i = i0 + tr * 4 + x;
-      if (i >= it.m) break;
-      if (a.bf16) {
-        bf16_t* Lh = (bf16_t*)it.L + (size_t)i * 2 * RP + tc * CPT;
-        bf16_t* Ll = Lh + RP;
+    for (int j = 0; j < RP / 16; ++j) {
+      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int y = 0; y < CPT; y += 4) {
-          float v[4], lo[4];
+      for (int k = 0; k < RP / 16; ++k) {
+        const f32x4 sf = *(const f32x4*)&St[(16 * j + l16) * SP + 16 * k + 4 * g];
 #pragma unroll
-          for (int z = 0; z < 4; ++z) {
-            v[z] = a.lr * acc[x][y + z];
-            lo[z] = v[z] - bf16_to_f32(f32_to_bf16(v[z]));
-          }
-          *(u32x2*)(Lh + y) = (u32x2){pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
-          *(u32x2*)(Ll + y) = (u32x2){pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3])};
+        for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(sf[e], uf[k][e], acc, 0, 0, 0);
+      }
+      const int c = 16 * j + 4 * g;
+      float v[4], lo[4];
+#pragma unroll
+      for (int z = 0; z < 4; ++z) v[z] = a.lr * acc[z];
+      if (row < it.m) {
+        if (a.bf16) {
+          bf16_t* Lh = (bf16_t*)it.L + (size_t)row * 2 * RP + c;
+#pragma unroll
+          for (int z = 0; z < 4; ++z) lo[z] = v[z] - bf16_to_f32(f32_to_bf16(v[z]));
+          *(u32x2*)Lh = (u32x2){pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+          *(u32x2*)(Lh + RP) = (u32x2){pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3])};
+        } else {
+          // fp32 W keeps L unpadded: m x rp with rp == r.
+          float* Lf = (float*)it.L + (size_t)row * a.rp;
+#pragma unroll
+          for (int z = 0; z < 4; ++z)
+            if (c + z < a.rp) Lf[c + z] = v[z];
         }
-      } else {
-        // fp32 W keeps L unpadded: m x rp with rp == r.
-        float* Lf = (float*)it.L + (size_t)i * a.rp;
-#pragma unroll
-        for (int y = 0; y < CPT; ++y)
-          if (tc * CPT + y < a.rp) Lf[tc * CPT + y] = a.lr * acc[x][y];
       }
     }
   } else {
