@@ -17,7 +17,7 @@
 //                CUs otherwise) and for the narrow projection X V.  With FAN it goes on to form
 //                every block of a shared X from the tile of X W^T it holds.
 // Measured (before: one 64 x 64 tile kernel on the vector FMA, K in tiles of 16 staged a float at
-// a time): 8 blocks of 512 x 2048 x 2048, r = 16: 899 -> 302 us for the whole call (the product
+// a time): 8 blocks of 512 x 2048 x 2048, r = 16: 899 -> 287 us for the whole call (the product
 // 703 -> 290 us, 118 TFLOP/s); the projection of the same call 212 -> 12 us; 64 x 256 x 512 with
 // one X for 8 blocks 131 -> 21 us.
 // Operands need only be 4-byte aligned and K may be anything: rows are read 16 bytes at a time
@@ -105,6 +105,15 @@ __global__ __launch_bounds__(256, 2) void k_f32_tile(F32Args a) {
     const float* pa = m ? A : C;
     const float* pb = m ? B : D;
     const int K = m ? a.K : a.rc, k = (m ? t : t - ntm) * 32 + kc * 4;
+    if (k - kc * 4 + 32 <= K) {  // a whole tile (uniform): no per-lane check of the row's end
+#pragma unroll
+      for (int i = 0; i < CA; ++i)
+        ra[i] = (f32x4)*(const f32x4_a4*)(pa + (size_t)min(m0 + lrow + 32 * i, a.rows_a - 1) * K + k);
+#pragma unroll
+      for (int i = 0; i < CB; ++i)
+        rb[i] = (f32x4)*(const f32x4_a4*)(pb + (size_t)min(t0 + lrow + 32 * i, a.rows_b - 1) * K + k);
+      return;
+    }
 #pragma unroll
     for (int i = 0; i < CA; ++i) ra[i] = row4(pa + (size_t)min(m0 + lrow + 32 * i, a.rows_a - 1) * K, k, K);
 #pragma unroll
@@ -203,6 +212,18 @@ __global__ __launch_bounds__(256) void k_f32_split(F32Args a) {
     const float* pa = m ? A : C;
     const float* pb = m ? B : D;
     const int K = m ? a.K : a.rc, k = (m ? t : t - nsm) * 32 + 4 * fq;
+    if (k - 4 * fq + 32 <= K) {  // a whole slice (uniform)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+          s.fa[h][i] = (f32x4)*(const f32x4_a4*)(pa + (size_t)rowa[i] * K + k + 16 * h);
+#pragma unroll
+        for (int j = 0; j < TN; ++j)
+          s.fb[h][j] = (f32x4)*(const f32x4_a4*)(pb + (size_t)rowb[j] * K + k + 16 * h);
+      }
+      return;
+    }
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
 #pragma unroll
