@@ -181,7 +181,8 @@ int zo_subspace_refresh_noalloc(int count, const zo_panel* panels, int r,
  * near fp16's smallest normal), so it is ~2^-16 accurate relative to its own
  * size.  X_b V itself is formed by the input type's MFMA from a high + low
  * split of V (for fp16, of 256 V, scaled back exactly).  Outputs rounded to
- * nearest even.  fp32 inputs use fp32 FMA throughout.
+ * nearest even.  fp32 inputs use fp32 multiply-adds
+ * throughout (the fp32 MFMA).
  * Limits: 1 <= r <= ZO_MAX_RANK, 1 <= q <= ZO_MAX_QUERIES, 1 <= nblk <=
  * ZO_MAX_BLOCKS; 16-bit inputs need m % 8 == 0 and n % 8 == 0; fp16 inputs
  * need |V| < 255 entrywise (a column-orthonormal V has |V| <= 1; larger
