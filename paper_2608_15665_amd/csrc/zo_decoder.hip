@@ -36,7 +36,8 @@
 // ~2^-16 accurate before the output's rounding; P is computed as
 // 2^(s scale - m + 12) (the common factor cancels in the normalisation and keeps
 // fp16 low parts out of the subnormal range), with the running maximum m, a
-// whole number in log2 units, moved only when a logit exceeds it by more than 3.
+// whole number in log2 units (a raw logit where those get coarse), moved only
+// when a logit exceeds it by more than 3.
 //
 // What bounds it: a wave's tile is a chain (S, maximum, exponentials, conversion, P V) of about 1500
 // matrix and 1600 vector cycles, and two or three waves per SIMD do not hide it.  So tile n + 1's S
@@ -44,9 +45,9 @@
 // nothing but the last tile of a wave is masked, and 4-wave workgroups run out of step with
 // each other.  The workgroups of one K/V (query tiles, grouped heads) run on one XCD.
 // Before (8 waves in step, no overlap, K/V fetched per query tile) and now:
-//   OPT-13B layer, 16 x 8192 x 40 x 128, 512 keys: 2326 -> 2068 us (333 TFLOP/s of visible pairs)
-//   8 x 4096 x 32 x 128, 256 keys: 279 -> 262;  ... x 64: 155 -> 138
-//   fp16, 8 x 8192 x 20 x 64, 2048 keys: 1418 -> 700;  4 x 8192 x 20 (4 KV) x 128, 1024 keys: 526 -> 398
+//   OPT-13B layer, 16 x 8192 x 40 x 128, 512 keys: 2325 -> 2083 us (331 TFLOP/s of visible pairs)
+//   8 x 4096 x 32 x 128, 256 keys: 277 -> 268;  ... x 64: 155 -> 140
+//   fp16, 8 x 8192 x 20 x 64, 2048 keys: 1406 -> 725;  4 x 8192 x 20 (4 KV) x 128, 1024 keys: 525 -> 397
 #include "zo_internal.h"
 
 #include <type_traits>
@@ -329,6 +330,11 @@ __device__ __forceinline__ float max_groups(float x) {
   return fmaxf(__uint_as_float(b[0]), __uint_as_float(b[1]));
 }
 
+// Whether a running maximum m is a whole number in log2 units (see k_attention's softmax).  The scale is
+// at most log2(e) / 8, so a raw logit that stands for 2^22 log2 units or more is not below 2^22 itself.
+constexpr float AT_WHOLE = 4194304.f;
+__device__ __forceinline__ bool at_whole(float m) { return fabsf(m) < AT_WHOLE; }
+
 template <bool F16, int DH>
 __global__ __launch_bounds__(64 * AT_W, DH == 64 ? 3 : 2) void k_attention(AttnArgs a) {
   constexpr int W = AT_W, NT = 64 * W;  // waves, threads
@@ -385,7 +391,7 @@ __global__ __launch_bounds__(64 * AT_W, DH == 64 ? 3 : 2) void k_attention(AttnA
   for (int gq = 0; gq < AT_NG; ++gq) {
 #pragma unroll
     for (int t = 0; t < DT; ++t) o[gq][t] = (f32x4){0.f, 0.f, 0.f, 0.f};
-    mrow[gq] = -1e30f;  // running maximum of the logits in log2 units, a whole number once set
+    mrow[gq] = -1e30f;  // running maximum of the logits (at_whole: in log2 units, else raw)
     lsum[gq] = 0.f;     // this lane's part of the running sum
   }
 
@@ -421,6 +427,7 @@ __global__ __launch_bounds__(64 * AT_W, DH == 64 ? 3 : 2) void k_attention(AttnA
     }
   };
   f32x4 sa[AT_NG][4];  // S^T of the tile at hand
+  int raw = 0;  // whether the wave has a running maximum that is a raw logit
   // One tile of the wave: softmax and P V of st's tile.  NEXT: also the next tile's S^T (into sn, from
   // kn).  Its MFMAs have no part in this tile's chain (maximum, exponentials, conversion, P V), so
   // they run under the first half's exponentials, and the first half's P V under the second half's.
@@ -429,10 +436,14 @@ __global__ __launch_bounds__(64 * AT_W, DH == 64 ? 3 : 2) void k_attention(AttnA
   auto tile = [&](auto NEXT, int k0, const uint16_t* kn, f32x4 (*st)[4], f32x4 (*sn)[4]) {
     constexpr bool next = decltype(NEXT)::value;
     // Online softmax: P = 2^(s scale - m + 12) as hi + lo 16-bit pairs in the B-operand order of the
-    // P V MFMA.  m is a whole number, so 12 - m and the rescale factor 2^(m - m') are exact and each
-    // exponent is one fused multiply-add.  It moves only when some query of the wave has a logit
-    // more than 3 (log2 units) above it, so most tiles skip the rescale of O; P then stays at or
-    // below 2^15 (within fp16's range), and the first tile sets m to its row maximum rounded up.
+    // P V MFMA.  m is a whole number below AT_WHOLE, so 12 - m and the rescale factor 2^(m - m') are
+    // exact and each exponent is one fused multiply-add.  From there on, where s scale and m would be
+    // rounded apart (from 2^26 by whole powers of two), a row's m is the raw logit and its exponent
+    // (s - m) scale + 12, whose difference is exact near the maximum: P is 2^12 there at any magnitude.
+    // m moves only when some query of the wave has a logit more than 3 (log2 units) above it, so most
+    // tiles skip the rescale of O; P then stays at or below 2^15 (within fp16's range), and the first
+    // tile sets m to its row maximum (a whole one rounded up).  OPT-13B layer: 2083 us; 2229 with
+    // raw maxima alone; 2048 with whole ones alone, which cannot hold such logits.
     float cadd[AT_NG];
 #pragma unroll
     for (int gq = 0; gq < AT_NG; ++gq) {
@@ -445,15 +456,34 @@ __global__ __launch_bounds__(64 * AT_W, DH == 64 ? 3 : 2) void k_attention(AttnA
           tmax = fmaxf(tmax, st[gq][t][i]);
         }
       tmax = max_groups(tmax);
-      if (__ballot(fmaf(tmax, a.scale_log2, -mrow[gq]) > 3.f)) {
-        const float mnew = fmaxf(mrow[gq], ceilf(tmax * a.scale_log2));
-        const float alpha = __builtin_amdgcn_exp2f(mrow[gq] - mnew);
+      const float m = mrow[gq];
+      float over = fmaf(tmax, a.scale_log2, -m);
+      if (__builtin_expect(raw, 0) && !at_whole(m)) over = (tmax - m) * a.scale_log2;
+      if (__builtin_expect(__ballot(over > 3.f) != 0, 0)) {
+        float mnew = m;
+        if (over > 0.f) {
+          mnew = ceilf(tmax * a.scale_log2);
+          if (!at_whole(mnew)) mnew = tmax;
+        }
+        const float alpha = __builtin_amdgcn_exp2f(
+            fmaf((at_whole(m) ? 0.f : m) - (at_whole(mnew) ? 0.f : mnew), a.scale_log2,
+                 (at_whole(m) ? m : 0.f) - (at_whole(mnew) ? mnew : 0.f)));
         mrow[gq] = mnew;
+        raw |= __ballot(!at_whole(mnew)) != 0;
         lsum[gq] *= alpha;
 #pragma unroll
         for (int t = 0; t < DT; ++t) o[gq][t] *= alpha;
       }
       cadd[gq] = 12.f - mrow[gq];
+    }
+    if (__builtin_expect(raw, 0)) {
+#pragma unroll
+      for (int gq = 0; gq < AT_NG; ++gq)
+        if (!at_whole(mrow[gq])) {
+          cadd[gq] = 12.f;
+#pragma unroll
+          for (int t = 0; t < 4; ++t) st[gq][t] -= mrow[gq];
+        }
     }
     // P of 32-key chunk c (subtiles 2 c and 2 c + 1), as the two B operands per query group.
     bf16x8 bh[2][AT_NG], bl[2][AT_NG];

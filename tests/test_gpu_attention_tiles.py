@@ -34,3 +34,44 @@ def test_attention_tile_edges(seq, heads, kv, dh, shape, dt):
     for b in range(nblk):
         sl = slice(b * T, (b + 1) * T)
         check_attention(got[sl], Qv[sl], Kv[sl], Vv[sl], heads, seq, dt, (b, shape), kv)
+
+
+@pytest.mark.parametrize("dt,c", [("f16", 506.0), ("f16", 1000.0), ("f16", 2048.0), ("f16", 2056.0), ("f16", 8192.0), ("f16", 16376.0),
+                                  ("bf16", 512.0), ("bf16", 1024.0), ("bf16", 8192.0), ("bf16", 2.0 ** 20), ("bf16", 2.0 ** 45)])
+@pytest.mark.parametrize("dh", [64, 128])
+def test_attention_huge_logits(dh, dt, c):
+    """Logits up to dh c^2 (finite in fp32), where a rounding of s scale alone is worth whole powers of
+    two; the smaller c put the running maximum on both sides of 2^22, where its form changes.  Equal
+    keys have equal logits, so their average is an ordinary one; otherwise the logits differ by so much
+    that one key has all the weight, and the output is its row of V bit for bit."""
+    rng = np.random.default_rng(dh)
+
+    def run(q, k, v):
+        seq = len(k)
+        (Qd, Qv), (Kd, Kv), (Vd, Vv) = (cast(np.tile(x, (2, 1)), dt) for x in (q, k, v))
+        O = torch.full_like(Qd, float("nan"))
+        zo.causal_attention(Qd, Kd, Vd, 1, 2 * seq, seq, 1, out=O)
+        return host(O), Qv, Kv, Vv
+
+    for seq in (1, 2, 70, 200):  # all keys equal
+        full = np.full((seq, dh), c)
+        O, Qv, Kv, Vv = run(full, full, rng.standard_normal((seq, dh)))
+        check_attention(O, Qv, Kv, Vv, 1, seq, dt, (c, seq))
+        np.testing.assert_array_equal(O[::seq], Vv[::seq])  # the first query sees one key
+    seq = 200
+    full, v = np.full((seq, dh), c), rng.standard_normal((seq, dh))
+    top = 77  # one dominant key, after which every query takes its row; before it, key 0 dominates
+    k = np.full((seq, dh), c / 4)
+    k[0], k[top] = c / 2, c
+    O, _, _, Vv = run(full, k, v)
+    want = np.where((np.arange(2 * seq) % seq < top)[:, None], Vv[0], Vv[top])
+    np.testing.assert_array_equal(O, want)
+    # each key above all before it (the running maximum moves in every tile): a query takes its own row
+    O, _, _, Vv = run(full, full * (np.arange(1, seq + 1) / 256)[:, None], v)
+    np.testing.assert_array_equal(O, Vv)
+    # the same from far below zero
+    O, _, _, Vv = run(full, -full * (np.arange(seq, 0, -1) / 256)[:, None], v)
+    np.testing.assert_array_equal(O, Vv)
+    # all logits far below zero, the first the largest
+    O, _, _, Vv = run(full, -full * (np.arange(1, seq + 1) / 256)[:, None], v)
+    np.testing.assert_array_equal(O, np.broadcast_to(Vv[0], Vv.shape))
