@@ -15,7 +15,7 @@
 // by each pass from L1/L2 (k_layernorm).  Both do the same operations in the
 // same order, so their results are identical.
 //
-// k_attention<F16, DH>: one workgroup of 4 waves per (block, sequence, head, tile
+// k_attention<F16, DH, ONE>: one workgroup of 4 waves per (block, sequence, head, tile
 // of 128 queries); keys in tiles of 64 through LDS (both K and V stored
 // row-major), online softmax in fp32.  Each wave owns AT_NG = 2 groups of 16
 // queries that share every K and V fragment it reads from LDS, skips the
@@ -335,7 +335,8 @@ __device__ __forceinline__ float max_groups(float x) {
 constexpr float AT_WHOLE = 4194304.f;
 __device__ __forceinline__ bool at_whole(float m) { return fabsf(m) < AT_WHOLE; }
 
-template <bool F16, int DH>
+// ONE: sequences of at most one tile of keys.
+template <bool F16, int DH, bool ONE>
 __global__ __launch_bounds__(64 * AT_W, DH == 64 ? 3 : 2) void k_attention(AttnArgs a) {
   constexpr int W = AT_W, NT = 64 * W;  // waves, threads
   constexpr int AT_Q = 16 * AT_NG * W;  // queries per workgroup
@@ -347,7 +348,7 @@ __global__ __launch_bounds__(64 * AT_W, DH == 64 ? 3 : 2) void k_attention(AttnA
   constexpr int C8 = DH / 8;          // 16-byte chunks per head row
   constexpr int KCH = AT_K * C8 / NT;    // K (and V) chunks per thread per tile
   static_assert(KCH * NT == AT_K * C8, "tile / thread mismatch");
-  __shared__ __attribute__((aligned(16))) uint16_t Ks[2][AT_K * KROW];
+  __shared__ __attribute__((aligned(16))) uint16_t Ks[ONE ? 1 : 2][AT_K * KROW];
   __shared__ __attribute__((aligned(16))) uint16_t Vs[AT_K * VROW];
 
   // Workgroup -> (block, sequence, head, query tile).  The hardware deals workgroup w to XCD w % 8;
@@ -548,62 +549,94 @@ __global__ __launch_bounds__(64 * AT_W, DH == 64 ? 3 : 2) void k_attention(AttnA
     pv(1);
   };
 
-  const int kend = min(a.seq_len, q0 + AT_Q);  // keys beyond the tile's last query are never seen
-  load_tile(Kg, 0, kreg);
-  store_tile(Ks[0], KROW, kreg);
-  load_tile(Vg, 0, vreg);
-  if (AT_K < kend) load_tile(Kg, AT_K, kreg);
-  __syncthreads();
-#pragma unroll
-  for (int t = 0; t < 4; ++t) qk(Ks[0], t, sa);
-  const int klast = min(wq0 + 16 * AT_NG, kend);  // the wave's tiles start below this
-  for (int k0 = 0, n = 0; k0 < kend; k0 += AT_K, ++n) {
-    // V(n) and K(n + 1) to LDS; K(n + 2) and V(n + 1) on their way.
-    uint16_t* const kn = Ks[(n + 1) & 1];
-    if (n) __syncthreads();  // tile n - 1 has been consumed
+  if constexpr (ONE) {
+    // No next tile: nothing is staged ahead and the rows are stored from the registers, so one barrier
+    // and half the registers do (94 to 143: three to five waves per SIMD), where the loop below makes
+    // such calls wait on its barriers.  4 x 2048 x 20 x 128, us, before the loop / loop / this: 16 keys
+    // 91 / 103 / 42, 48 keys 41.8 / 43.4 / 29.7, 64 keys 37.2 / 34.8 / 31.2.
+    load_tile(Kg, 0, kreg);
+    load_tile(Vg, 0, vreg);
+    store_tile(Ks[0], KROW, kreg);
     store_tile(Vs, VROW, vreg);
-    if (k0 + AT_K < kend) store_tile(kn, KROW, kreg);
     __syncthreads();
-    if (k0 + AT_K < kend) load_tile(Vg, k0 + AT_K, vreg);
-    if (k0 + 2 * AT_K < kend) load_tile(Kg, k0 + 2 * AT_K, kreg);
-    if (k0 >= klast) continue;  // every key of the tile is after the wave's queries
-    if (k0 + AT_K < klast) {
-      f32x4 sn[AT_NG][4];
-      tile(std::true_type{}, k0, kn, sa, sn);
+    if (wq0 >= a.seq_len) return;
 #pragma unroll
-      for (int gq = 0; gq < AT_NG; ++gq)
+    for (int t = 0; t < 4; ++t) qk(Ks[0], t, sa);
+    tile(std::false_type{}, 0, Ks[0], sa, sa);
 #pragma unroll
-        for (int t = 0; t < 4; ++t) sa[gq][t] = sn[gq][t];
-    } else {
-      tile(std::false_type{}, k0, kn, sa, sa);
+    for (int gq = 0; gq < AT_NG; ++gq) {
+      float l = lsum[gq] + __shfl_xor(lsum[gq], 16, 64);
+      l += __shfl_xor(l, 32, 64);
+      if (myq[gq] >= a.seq_len) continue;
+      const float inv = 1.f / l;
+      uint16_t* op = (uint16_t*)a.O + (size_t)(row0 + myq[gq]) * a.d + col0 + 4 * g;
+#pragma unroll
+      for (int t = 0; t < DT; ++t) {
+        const float y0 = o[gq][t][0] * inv, y1 = o[gq][t][1] * inv;
+        const float y2 = o[gq][t][2] * inv, y3 = o[gq][t][3] * inv;
+        *(u32x2*)(op + 16 * t) = F16 ? (u32x2){pack_f16x2(y0, y1), pack_f16x2(y2, y3)}
+                                     : (u32x2){pack_bf16x2(y0, y1), pack_bf16x2(y2, y3)};
+      }
     }
-  }
-  // Normalise by the row sums (over the 4 lane groups).  Rows go through LDS (the K buffers, no longer
-  // needed) so that a store covers whole 2 DH-byte rows instead of 16 pieces of 32 bytes.
-  __syncthreads();
-  uint16_t* const ow = Ks[0] + wave * 16 * AT_NG * KROW;
-  static_assert(16 * AT_NG * W * KROW <= 2 * AT_K * KROW, "the staged rows fit the K buffers");
+    return;
+  } else {
+    const int kend = min(a.seq_len, q0 + AT_Q);  // keys beyond the tile's last query are never seen
+    load_tile(Kg, 0, kreg);
+    store_tile(Ks[0], KROW, kreg);
+    load_tile(Vg, 0, vreg);
+    if (AT_K < kend) load_tile(Kg, AT_K, kreg);
+    __syncthreads();
 #pragma unroll
-  for (int gq = 0; gq < AT_NG; ++gq) {
-    float l = lsum[gq] + __shfl_xor(lsum[gq], 16, 64);
-    l += __shfl_xor(l, 32, 64);
-    const float inv = 1.f / l;
+    for (int t = 0; t < 4; ++t) qk(Ks[0], t, sa);
+    const int klast = min(wq0 + 16 * AT_NG, kend);  // the wave's tiles start below this
+    for (int k0 = 0, n = 0; k0 < kend; k0 += AT_K, ++n) {
+      // V(n) and K(n + 1) to LDS; K(n + 2) and V(n + 1) on their way.
+      uint16_t* const kn = Ks[(n + 1) & 1];
+      if (n) __syncthreads();  // tile n - 1 has been consumed
+      store_tile(Vs, VROW, vreg);
+      if (k0 + AT_K < kend) store_tile(kn, KROW, kreg);
+      __syncthreads();
+      if (k0 + AT_K < kend) load_tile(Vg, k0 + AT_K, vreg);
+      if (k0 + 2 * AT_K < kend) load_tile(Kg, k0 + 2 * AT_K, kreg);
+      if (k0 >= klast) continue;  // every key of the tile is after the wave's queries
+      if (k0 + AT_K < klast) {
+        f32x4 sn[AT_NG][4];
+        tile(std::true_type{}, k0, kn, sa, sn);
 #pragma unroll
-    for (int t = 0; t < DT; ++t) {
-      const float y0 = o[gq][t][0] * inv, y1 = o[gq][t][1] * inv;
-      const float y2 = o[gq][t][2] * inv, y3 = o[gq][t][3] * inv;
-      const u32x2 pk = F16 ? (u32x2){pack_f16x2(y0, y1), pack_f16x2(y2, y3)}
-                           : (u32x2){pack_bf16x2(y0, y1), pack_bf16x2(y2, y3)};
-      *(u32x2*)&ow[(16 * gq + l16) * KROW + 16 * t + 4 * g] = pk;
+        for (int gq = 0; gq < AT_NG; ++gq)
+#pragma unroll
+          for (int t = 0; t < 4; ++t) sa[gq][t] = sn[gq][t];
+      } else {
+        tile(std::false_type{}, k0, kn, sa, sa);
+      }
     }
-  }
-  // Each wave reads back only its own rows.
+    // Normalise by the row sums (over the 4 lane groups).  Rows go through LDS (the K buffers, no longer
+    // needed) so that a store covers whole 2 DH-byte rows instead of 16 pieces of 32 bytes.
+    __syncthreads();
+    uint16_t* const ow = Ks[0] + wave * 16 * AT_NG * KROW;
+    static_assert(16 * AT_NG * W * KROW <= 2 * AT_K * KROW, "the staged rows fit the K buffers");
 #pragma unroll
-  for (int x = lane; x < 16 * AT_NG * C8; x += 64) {
-    const int row = x / C8, c = x % C8;
-    const u32x4 v = *(const u32x4*)&ow[row * KROW + 8 * c];
-    if (wq0 + row < a.seq_len)
-      *(u32x4*)((uint16_t*)a.O + (size_t)(row0 + wq0 + row) * a.d + col0 + 8 * c) = v;
+    for (int gq = 0; gq < AT_NG; ++gq) {
+      float l = lsum[gq] + __shfl_xor(lsum[gq], 16, 64);
+      l += __shfl_xor(l, 32, 64);
+      const float inv = 1.f / l;
+#pragma unroll
+      for (int t = 0; t < DT; ++t) {
+        const float y0 = o[gq][t][0] * inv, y1 = o[gq][t][1] * inv;
+        const float y2 = o[gq][t][2] * inv, y3 = o[gq][t][3] * inv;
+        const u32x2 pk = F16 ? (u32x2){pack_f16x2(y0, y1), pack_f16x2(y2, y3)}
+                             : (u32x2){pack_bf16x2(y0, y1), pack_bf16x2(y2, y3)};
+        *(u32x2*)&ow[(16 * gq + l16) * KROW + 16 * t + 4 * g] = pk;
+      }
+    }
+    // Each wave reads back only its own rows.
+#pragma unroll
+    for (int x = lane; x < 16 * AT_NG * C8; x += 64) {
+      const int row = x / C8, c = x % C8;
+      const u32x4 v = *(const u32x4*)&ow[row * KROW + 8 * c];
+      if (wq0 + row < a.seq_len)
+        *(u32x4*)((uint16_t*)a.O + (size_t)(row0 + wq0 + row) * a.d + col0 + 8 * c) = v;
+    }
   }
 }
 
@@ -693,11 +726,13 @@ int zo_attention_launch(int nblk, int T, int seq_len, int d, int heads, int kv_h
   }
   const dim3 grid((unsigned)wg), block(64 * AT_W);
   const bool f16 = dtype == ZO_F16;
-#define ZO_ATTN(F, D) hipLaunchKernelGGL((k_attention<F, D>), grid, block, 0, stream, a)
+#define ZO_ATTN(F, D)                                                                            \
+  if (seq_len <= AT_K) hipLaunchKernelGGL((k_attention<F, D, true>), grid, block, 0, stream, a); \
+  else hipLaunchKernelGGL((k_attention<F, D, false>), grid, block, 0, stream, a)
   if (dh == 64) {
-    if (f16) ZO_ATTN(true, 64); else ZO_ATTN(false, 64);
+    if (f16) { ZO_ATTN(true, 64); } else { ZO_ATTN(false, 64); }
   } else {
-    if (f16) ZO_ATTN(true, 128); else ZO_ATTN(false, 128);
+    if (f16) { ZO_ATTN(true, 128); } else { ZO_ATTN(false, 128); }
   }
 #undef ZO_ATTN
   return zo_hip_status(hipGetLastError(), "k_attention");

@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("dt", ["bf16", "f16"])
-@pytest.mark.parametrize("seq", [1, 31, 32, 33, 63, 64, 65, 96, 127, 128, 129, 160, 193, 257, 520])
+@pytest.mark.parametrize("seq", [1, 15, 16, 17, 31, 32, 33, 47, 48, 49, 63, 64, 65, 96, 127, 128, 129, 160, 193, 257, 520])
 @pytest.mark.parametrize("heads,kv,dh,shape", [(2, 2, 64, "plain"), (4, 2, 128, "rise"), (3, 1, 64, "fall"),
                                                (2, 1, 128, "large")])
 def test_attention_tile_edges(seq, heads, kv, dh, shape, dt):
@@ -53,7 +53,7 @@ def test_attention_huge_logits(dh, dt, c):
         zo.causal_attention(Qd, Kd, Vd, 1, 2 * seq, seq, 1, out=O)
         return host(O), Qv, Kv, Vv
 
-    for seq in (1, 2, 70, 200):  # all keys equal
+    for seq in (1, 2, 48, 64, 70, 200):  # all keys equal
         full = np.full((seq, dh), c)
         O, Qv, Kv, Vv = run(full, full, rng.standard_normal((seq, dh)))
         check_attention(O, Qv, Kv, Vv, 1, seq, dt, (c, seq))
