@@ -101,8 +101,8 @@ const char* zo_last_error_detail(void);
  * configuration here) reach such a condition with probability below 1e-30.
  *
  *   omega   device, rows x r fp32, row-major; read only.
- *   q       device, rows x r fp32 output; may alias omega.  Where it does not, it may
- *           hold partial sums while the call runs.
+ *   q       device, rows x r fp32 output; may alias omega.  Where it overlaps nothing
+ *           else of the call, it may hold partial sums while the call runs.
  *   r_diag  device, r fp32 output (diag of the corrected R, > 0); nullable.
  *   info    device, `count` ints, nullable: info[p] = 0, or k+1 when the
  *           first Cholesky pivot that is not positive is at column k

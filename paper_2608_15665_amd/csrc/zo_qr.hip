@@ -33,9 +33,10 @@
 // a few panels (one OPT-13B layer: 50 workgroups; an OPT-1.3B layer at r = 128: 18), so a call with
 // fewer than FEW_WG of them takes 512-row (r <= 64) or 256-row chunks.  Their partials go to the
 // panel's own output Q, which nothing reads or writes before the last pass fills it (the
-// workspace's size is a promise, and the no-allocation variant's scratch is fixed); where an output
-// overlaps an Omega of the call, or is too small, the call keeps the long chunks.  A panel's sum is
-// the same tree either way (units of 128 or 256 rows, added in order within 2048 rows, then the
+// workspace's size is a promise, and the no-allocation variant's scratch is fixed).  Where one output
+// of the call overlaps an Omega, another output, diag(R) or info, or is smaller than its partials (few
+// rows; any rows at r = 1 and at 65 <= r <= 72, whose tiles are padded to 128 columns), the whole call
+// keeps the long chunks.  A panel's sum is the same tree either way (units of 128 or 256 rows, added in order within 2048 rows, then the
 // 2048-row sums in order), so its Q is the same bits whatever else the call holds.
 //
 // Measured, whole call, before (a factorisation column by column in LDS, 2048- and 1024-row chunks,
@@ -622,8 +623,9 @@ size_t panel_ws(int rows, int RK) {
 }
 
 // Whether the call takes short chunks of `chunk` rows, their partials in the panels' outputs: too few
-// long chunks to fill the chip, every output large enough, and none over an Omega.
-bool short_chunks(int count, const zo_panel* panels, int r, int RK, int chunk) {
+// long chunks to fill the chip, every output large enough, and none over anything else that the
+// call reads or writes (an Omega, another panel's output, diag(R), info).
+bool short_chunks(int count, const zo_panel* panels, int r, int RK, int chunk, const int* info) {
   if (count > FEW_PANELS) return false;
   long long wg = 0;
   for (int p = 0; p < count; ++p) {
@@ -632,9 +634,12 @@ bool short_chunks(int count, const zo_panel* panels, int r, int RK, int chunk) {
     const size_t q_bytes = (size_t)e.rows * r * 4, nchunk = (size_t)((e.rows + chunk - 1) / chunk);
     if (wg >= FEW_WG || nchunk * part_bytes(RK) + 8 > q_bytes) return false;
     const uintptr_t q0 = (uintptr_t)e.q, q1 = q0 + q_bytes;
+    auto over = [&](const void* a, size_t bytes) { return a && q0 < (uintptr_t)a + bytes && (uintptr_t)a < q1; };
+    if (over(info, (size_t)count * 4)) return false;
     for (int o = 0; o < count; ++o) {
-      const uintptr_t a0 = (uintptr_t)panels[o].omega, a1 = a0 + (size_t)panels[o].rows * r * 4;
-      if (q0 < a1 && a0 < q1) return false;
+      const size_t bytes = (size_t)panels[o].rows * r * 4;
+      if (over(panels[o].omega, bytes) || over(panels[o].r_diag, (size_t)r * 4)) return false;
+      if (o != p && over(panels[o].q, bytes)) return false;
     }
   }
   return true;
@@ -687,7 +692,7 @@ int zo_refresh_launch(int count, const zo_panel* panels, int r, int* info, void*
     return ZO_ERR_WORKSPACE;
   }
   const int fine = r > 64 ? WUNIT : FINE;
-  const int chunk = short_chunks(count, panels, r, RK, fine) ? fine : CHUNK;
+  const int chunk = short_chunks(count, panels, r, RK, fine, info) ? fine : CHUNK;
   WsCarver wc(ws);
   CqrPanel* tab = (CqrPanel*)wc.take((size_t)count * sizeof(CqrPanel));
   std::vector<CqrPanel> host((size_t)count);

@@ -33,25 +33,26 @@ def _ref(om):
     return Q * s, np.abs(np.diag(R))
 
 
+def run(om, r, out, rd=None, info=None):
+    n = len(om)
+    rd = [torch.empty(r, device="cuda") for _ in range(n)] if rd is None else rd
+    info = torch.full((n,), -1, dtype=torch.int32, device="cuda") if info is None else info
+    zo.subspace_refresh(om, r, out=out, r_diag=rd, info=info)
+    return [o.cpu().numpy() for o in out], [d.cpu().numpy() for d in rd], info.cpu().numpy()
+
+
 @pytest.mark.parametrize("r", sorted(ROWS))
 def test_chunks_agree_bitwise_and_with_householder(r):
     rng = np.random.default_rng(r)
     host = [rng.standard_normal((rows, r)).astype(np.float32) for rows in ROWS[r]]
     oms = [dev_f32(h) for h in host]
 
-    def run(om, out, many=False):
-        n = len(om)
-        rd = [torch.empty(r, device="cuda") for _ in range(n)]
-        info = torch.full((n,), -1, dtype=torch.int32, device="cuda")
-        zo.subspace_refresh(om, r, out=out, r_diag=rd, info=info)
-        return [o.cpu().numpy() for o in out], [d.cpu().numpy() for d in rd], info.cpu().numpy()
-
-    alone, rda, infa = run(oms, [torch.full_like(o, float("nan")) for o in oms])
+    alone, rda, infa = run(oms, r, [torch.full_like(o, float("nan")) for o in oms])
     place = [o.clone() for o in oms]
-    inpl, rdi, infi = run(place, place)
+    inpl, rdi, infi = run(place, r, place)
     filler = dev_f32(rng.standard_normal((max(r, 32), r)))
     crowd = oms + [filler] * 70  # more panels than a call with short chunks holds
-    many, rdm, _ = run(crowd, [torch.empty_like(o) for o in crowd])
+    many, rdm, _ = run(crowd, r, [torch.empty_like(o) for o in crowd])
     for p, h in enumerate(host):
         for q, d in ((inpl, rdi), (many, rdm)):
             np.testing.assert_array_equal(alone[p].view(np.uint32), q[p].view(np.uint32), err_msg=str(h.shape))
@@ -61,3 +62,43 @@ def test_chunks_agree_bitwise_and_with_householder(r):
             assert np.abs(alone[p] - Q).max() <= 1e-5 and normwise(alone[p], Q) <= 2e-7, h.shape
             assert normwise(rda[p], R) <= 2e-7
     assert not infa.any() and not infi.any()
+
+
+@pytest.mark.parametrize("r,sizes", [(64, [5120, 2050, 300]), (17, [4097, 600, 511]), (128, [4100, 2048, 500])])
+def test_outputs_that_overlap(r, sizes):
+    """One scratch output for every panel of a call that wants diag(R) and info only, and diag(R) or info
+    inside another panel's output: each value that the call leaves whole is that of separate calls."""
+    rng = np.random.default_rng(r + 1)
+    oms = [dev_f32(rng.standard_normal((rows, r))) for rows in sizes]
+    oms[1][:, r // 2] = 0  # one rank-deficient panel, so that info differs
+    ref = [run([o], r, [torch.empty_like(o)]) for o in oms]
+    refq, refd, refi = ([x[k][0] for x in ref] for k in range(3))
+    assert [int(i) for i in refi] == [0, r // 2 + 1, 0]
+    same = lambda a, b: np.testing.assert_array_equal(a.view(np.uint32), b.view(np.uint32))  # noqa: E731
+
+    scratch = torch.empty(max(sizes) * r, device="cuda")
+    _, rd, info = run(oms, r, [scratch[:o.numel()].view(o.shape) for o in oms])
+    assert list(info) == list(refi)
+    for p in range(3):
+        same(rd[p], refd[p])
+    # A panel's rows shifted into the next one's output: only the last written is whole.
+    _, rd, info = run(oms, r, [scratch[4 * p:4 * p + o.numel()].view(o.shape) for p, o in enumerate(oms)])
+    assert list(info) == list(refi)
+    for p in range(3):
+        same(rd[p], refd[p])
+
+    for p in range(3):  # the outputs are written last: whole, over whatever lay in them
+        out = [torch.empty_like(o) for o in oms]
+        rds = [torch.empty(r, device="cuda") for _ in oms]
+        rds[(p + 1) % 3] = out[p].view(-1)[8:8 + r]
+        q, rd, info = run(oms, r, out, rd=rds)
+        assert list(info) == list(refi)
+        for k in range(3):
+            same(q[k], refq[k])
+            if k != (p + 1) % 3:
+                same(rd[k], refd[k])
+        out = [torch.empty_like(o) for o in oms]
+        q, rd, _ = run(oms, r, out, info=out[p].view(-1)[4:7].view(torch.int32))
+        for k in range(3):
+            same(q[k], refq[k])
+            same(rd[k], refd[k])
