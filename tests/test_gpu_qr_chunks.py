@@ -1,8 +1,9 @@
 """The refresh's short and long row chunks, and its two row kernels (r <= 64 and r <= 128).
 
 A panel's sums are the same tree whatever the chunk length, so its Q, diag(R) and info are the same
-bits alone (short chunks, partials in its output), in place (long chunks: the output lies over
-Omega) and among enough panels to make the call take long chunks; and against a float64 Householder
+bits in a call of few panels (short chunks, partials in their outputs, where every output holds its
+partials: SHORT; long ones in ROWS, whose smallest panels do not), in place (long chunks: the output
+lies over Omega) and among enough panels to make the call take long chunks; and against a float64 Householder
 QR with the sign fix at the refresh's bar (1e-5 elementwise; the factor is exact to fp32 rounding,
 so 2e-7 normwise holds with room).  Rows sit on the edges of the units (128 and 256 rows), the short
 chunks (512 and 256) and the long ones (2048)."""
@@ -16,7 +17,7 @@ from _common import dev_f32, normwise
 pytestmark = pytest.mark.gpu
 
 ROWS = {
-    1: [1, 7, 512, 513, 2049],        # an output smaller than its partials: long chunks
+    1: [1, 7, 512, 513, 2049],
     15: [15, 127, 128, 129, 4097],
     17: [511, 513, 2047, 6000],
     48: [48, 640, 2048],
@@ -24,6 +25,16 @@ ROWS = {
     65: [65, 255, 257, 2049],
     100: [128, 512, 4100],
     128: [128, 129, 2047, 2048, 8193],
+}
+SHORT = {  # from the fewest rows whose output holds the partials of its short chunks
+    2: [257, 2049],
+    15: [35, 127, 128, 129, 4097],
+    17: [91, 511, 513, 2047, 6000],
+    48: [65, 640, 2048, 2049],
+    64: [81, 2050, 5120, 8191],
+    73: [253, 2048, 5120],
+    100: [185, 512, 4100],
+    128: [145, 2047, 2048, 8193],
 }
 
 
@@ -41,10 +52,16 @@ def run(om, r, out, rd=None, info=None):
     return [o.cpu().numpy() for o in out], [d.cpu().numpy() for d in rd], info.cpu().numpy()
 
 
-@pytest.mark.parametrize("r", sorted(ROWS))
-def test_chunks_agree_bitwise_and_with_householder(r):
+def _holds_partials(rows, r):
+    chunk, tiles = (512, (r + 15) // 16) if r <= 64 else (256, 8)
+    return -(-rows // chunk) * (tiles * (tiles + 1) // 2) * 2048 + 8 <= rows * r * 4
+
+
+@pytest.mark.parametrize("r,sizes", sorted(ROWS.items()) + sorted(SHORT.items()))
+def test_chunks_agree_bitwise_and_with_householder(r, sizes):
+    assert all(_holds_partials(rows, r) for rows in sizes) == (SHORT.get(r) is sizes or r == 17)
     rng = np.random.default_rng(r)
-    host = [rng.standard_normal((rows, r)).astype(np.float32) for rows in ROWS[r]]
+    host = [rng.standard_normal((rows, r)).astype(np.float32) for rows in sizes]
     oms = [dev_f32(h) for h in host]
 
     alone, rda, infa = run(oms, r, [torch.full_like(o, float("nan")) for o in oms])
