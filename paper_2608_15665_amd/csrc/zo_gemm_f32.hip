@@ -18,13 +18,15 @@
 //                every block of a shared X from the tile of X W^T it holds.
 // Measured (before: one 64 x 64 tile kernel on the vector FMA, K in tiles of 16 staged a float at
 // a time): 8 blocks of 512 x 2048 x 2048, r = 16: 899 -> 287 us for the whole call (the product
-// 703 -> 290 us, 118 TFLOP/s); the projection of the same call 212 -> 12 us; 64 x 256 x 512 with
-// one X for 8 blocks 131 -> 21 us.
+// 703 -> 270 us, 127 TFLOP/s); the projection of the same call 212 -> 12 us; 64 x 256 x 512 with
+// one X for 8 blocks 131 -> 17 us.
 // Operands need only be 4-byte aligned and K may be anything: rows are read 16 bytes at a time
 // (4-byte alignment is enough for the hardware's 16-byte loads), the last K % 4 floats of a row
 // one by one, so nothing past a row's end is read for the last row.  Rows past the operand's end
 // read its last row and are not stored.
 #include "zo_internal.h"
+
+#include <algorithm>
 
 namespace {
 
@@ -179,7 +181,8 @@ __global__ __launch_bounds__(256, 2) void k_f32_tile(F32Args a) {
 
 // ---------------------------------------------------------------- K split over the waves
 // FAN: B is one X for every block.  The tile of X W^T, summed over the waves, stays in LDS as the
-// base, and wave w then forms blocks w, w + 4, ...: the rank-r term from zero, plus the base.
+// base, and the waves of the tile's workgroups (grid z) then deal the blocks out: the rank-r term from
+// zero, plus the base.
 template <int TM, int TN, bool FAN>
 __global__ __launch_bounds__(256) void k_f32_split(F32Args a) {
   constexpr int BM = 16 * TM, BN = 16 * TN;
@@ -187,7 +190,7 @@ __global__ __launch_bounds__(256) void k_f32_split(F32Args a) {
   __shared__ __attribute__((aligned(16))) f32x4 red[4][NP * 64];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int fr = lane & 15, fq = lane >> 4;
-  const int m0 = blockIdx.x * BM, t0 = blockIdx.y * BN, blk = blockIdx.z;
+  const int m0 = blockIdx.x * BM, t0 = blockIdx.y * BN, blk = FAN ? 0 : blockIdx.z;
   const float* __restrict__ A = a.A;
   const float* __restrict__ B = a.B + (long long)blk * a.b_block_stride;
   const float* __restrict__ C = a.ca + (long long)blk * a.ca_block_stride;
@@ -280,7 +283,7 @@ __global__ __launch_bounds__(256) void k_f32_split(F32Args a) {
         const int x = (i * TN + j) * 64 + lane;
         base[i][j] = ((red[0][x] + red[1][x]) + red[2][x]) + red[3][x];
       }
-    for (int b = wave; b < a.fan; b += 4) {
+    for (int b = __builtin_amdgcn_readfirstlane(blockIdx.z + gridDim.z * wave); b < a.fan; b += 4 * gridDim.z) {
       const float* __restrict__ Cb = a.ca + (long long)b * a.ca_block_stride;
       f32x4 d[TM][TN];
 #pragma unroll
@@ -330,10 +333,11 @@ int launch_tile(F32Args a, hipStream_t stream) {
   return zo_hip_status(hipGetLastError(), "k_f32_tile");
 }
 
+// wgs: workgroups per tile (FAN).
 template <int TM, int TN, bool FAN>
-int launch_split(const F32Args& a, hipStream_t stream) {
+int launch_split(const F32Args& a, hipStream_t stream, int wgs = 1) {
   const dim3 grid((a.rows_a + 16 * TM - 1) / (16 * TM), (a.rows_b + 16 * TN - 1) / (16 * TN),
-                  FAN ? 1 : a.nblk);
+                  FAN ? wgs : a.nblk);
   hipLaunchKernelGGL((k_f32_split<TM, TN, FAN>), grid, dim3(256), 0, stream, a);
   return zo_hip_status(hipGetLastError(), "k_f32_split");
 }
@@ -370,4 +374,15 @@ int zo_gemm_f32_narrow(const F32Args& a, hipStream_t stream) {
 
 bool zo_gemm_f32_fans(const F32Args& a) { return tiles(a, 64) < 256; }
 
-int zo_gemm_f32_fan(const F32Args& a, hipStream_t stream) { return launch_split<2, 2, true>(a, stream); }
+// Workgroups per tile: one per four blocks, a block for each wave, while the tiles leave CUs idle.  Each
+// forms X W^T anew, which costs nothing on an idle CU and counts on a busy one.  Whole call, us, one /
+// up to 256 workgroups in all (512 in all: the last but one 52, the last 61):
+//   64 x 256 x 512, r = 4: 8 blocks 18.5 / 17.1, 128 blocks 78 / 27;   1 x 256 x 512, 256: 105 / 31
+//   256 x 1024 x 2048, r = 16: 8 blocks 38.4 / 38.6, 32 blocks 51.5 / 51.2
+// (Every block in full on a copied X: 17.1, 68 and 96; 101 and 293.  The smallest call's apply alone is
+// 8.5 against 8.1, 9.9 with one workgroup per tile; at r = 128 the whole call 46.3 against 42.0.)
+int zo_gemm_f32_fan(const F32Args& a, hipStream_t stream) {
+  const long long t = (long long)((a.rows_a + 31) / 32) * ((a.rows_b + 31) / 32);
+  const long long wgs = std::max(1LL, std::min(256 / t, (a.fan + 3LL) / 4));
+  return launch_split<2, 2, true>(a, stream, (int)wgs);
+}

@@ -28,6 +28,9 @@ def _dev(a, off):
     (40, 50, 2049, 17, 1, True, 0, "relu"),      # projection of 32 columns, K = 64 slices + 1
     (100, 70, 130, 33, 2, False, 2, "residual"),  # projection of 48 columns
     (20, 140, 67, 65, 1, True, 1, "silu"),       # 80 columns
+    (17, 40, 33, 5, 3, True, 1, "residual"),     # ... 6 blocks dealt to 8 waves of a tile's two workgroups
+    (100, 300, 64, 20, 9, True, 0, "none"),      # 18 blocks to 20 waves of 5 workgroups
+    (300, 500, 40, 5, 10, True, 2, "relu"),      # 160 tiles: one workgroup each, 5 blocks per wave
     (260, 700, 45, 100, 4, False, 1, "none"),    # 64 x 64 tiles, projection of 112 columns
     (1500, 1030, 70, 8, 2, False, 3, "residual"),  # 128 x 128 tiles
     (1501, 1027, 34, 20, 1, True, 1, "relu"),    # shared X through the base
