@@ -30,8 +30,8 @@
 // (zo_gemm_f32.hip).
 //
 // The main GEMM (k_gemm_main) is described where it is defined.  The
-// register-staged GEMM (k_gemm_bf16: narrow projections k_proj does not take and
-// the fallback for operands beyond the main GEMM's descriptors) computes a BM x BN tile of Y_b^T
+// register-staged GEMM (k_gemm_bf16: products and projections with an operand beyond the buffer
+// descriptors of k_gemm_main and k_proj) computes a BM x BN tile of Y_b^T
 // with v_mfma_f32_32x32x16_bf16: the A operand is the W tile (rows = output
 // columns), the B operand the X tile (rows = tokens), both K-contiguous and
 // staged through LDS in 128-byte rows with an XOR swizzle of the 16-byte
@@ -1757,17 +1757,12 @@ static int launch_projection(const PlinearPlan& p, const void* X, const void* vt
   g.y_block_stride = (long long)p.T * rows_a;
   g.ldy = rows_a;
   g.out_dtype = ZO_F32;
-  // From 128 rows on, the main GEMM's pipeline (256 x 256 tiles: the 2 rp = 128 rows of one
-  // r = 64 factor fill half a tile, a stacked q, k, v projection 384 of 512 rows): it keeps the X
-  // stream and the MFMAs overlapped better than the register-staged kernel even with the idle
-  // rows (OPT-13B-shaped stack: prepare 130 -> 103 ms per step).  Otherwise 64 x 256 tiles;
-  // 64 x 128 when that leaves fewer than two workgroups per CU.  Tile shapes change no
-  // element's arithmetic.
+  // The main GEMM's pipeline (256 x 256 tiles): it keeps the X stream and the MFMAs overlapped even
+  // where the factor's rows leave part of a tile idle.  Operands beyond its descriptors take the
+  // register-staged kernel in 64 x 256 tiles (so do factors of 64 rows, which come here for no other
+  // reason).  Tile shapes change no element's arithmetic.
   const bool f16 = p.in_dtype == ZO_F16;
   if (rows_a >= 128 && main_gemm_fits(g)) return launch_gemm_main(g, f16, stream);
-  const long long tiles = (long long)p.nx * ((p.T + 255) / 256) * ((rows_a + 63) / 64);
-  if (tiles < 512)
-    return f16 ? launch_gemm_bf16<1, 4, 2, 1, true>(g, stream) : launch_gemm_bf16<1, 4, 2, 1, false>(g, stream);
   return f16 ? launch_gemm_bf16<1, 4, 2, 2, true>(g, stream) : launch_gemm_bf16<1, 4, 2, 2, false>(g, stream);
 }
 

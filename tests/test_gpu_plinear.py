@@ -122,7 +122,7 @@ def test_bf16_parity(T, m, n, r, q, nblk, shared, out):
 
 
 @pytest.mark.parametrize("T,m,n,r,q,nblk,shared", [
-    (300, 264, 200, 16, 2, 4, False),   # ragged tails; n % 32 != 0 takes the generic tile kernel
+    (300, 264, 200, 16, 2, 4, False),   # ragged tails; n % 32 != 0: K columns past the end read as zero
     (256, 512, 512, 64, 4, 8, False),   # exact tiles, r = 64 (the main kernel)
     (96, 520, 136, 24, 3, 6, True),     # r not a multiple of 16, shared X
     (513, 256, 1024, 4, 1, 2, False),   # one row past a tile
