@@ -28,6 +28,8 @@ pytestmark = pytest.mark.gpu
     (32790, 40, 50, 2, 1),       # 256-token tiles
     (32790, 136, 9, 2, 2),
     (32790, 32, 9, 2, 3),        # the main GEMM's stack
+    (32790, 40, 9, 2, 3),        # the main GEMM in fp32, combined apart: a ragged stack of 192 rows
+    (300, 72, 40, 2, 2),         # ... of 256 rows
 ])
 def test_projection_tiles(T, n, r, nblk, count, dt):
     m, q = 16, nblk
