@@ -79,7 +79,7 @@ struct Item {
   int l_tiles;      // k_us workgroups forming L (US_ROWS rows each); then V tiles (64 rows each)
   int us_wg;        // all k_us workgroups of the item
   int up_begin;     // first update workgroup of the item
-  int strips, rchunks;  // 16-bit W: 256-column strips x 512-row chunks
+  int strips, rchunks;  // 16-bit W: strips of upd_cols columns x chunks of upd_rows rows
 };
 
 struct FillArgs {
@@ -334,7 +334,7 @@ __global__ __launch_bounds__(256) void k_update_bf16(UpdArgs a) {
   // range of tiles, rastered in groups of UPD_GROUP row chunks: within a group
   // the row chunk runs fastest, then the strip.  The ~32 workgroups an XCD runs
   // at once then cover about 4 row chunks x 8 strips, so each chunk's L rows
-  // (128 KB at r = 64) and each strip's V fragments (64 KB) come from its L2
+  // (64 KB at r = 64) and each strip's V fragments (128 KB) come from its L2
   // after the first read, instead of once per workgroup.
   const int w = blockIdx.x, nt = a.pass_wg;
   const int xcd = w & 7, widx = w >> 3;
