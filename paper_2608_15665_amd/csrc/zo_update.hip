@@ -14,8 +14,8 @@
 //               to zbar_out.
 //   k_us        Reads the item's flags: if any entry was non-finite the item is
 //               skipped (state untouched).  Otherwise commits the new moments and
-//               forms L = lr U S (m x rp; tiles of 64 rows, fp32 MFMA) and, for 16-bit W, the hi/lo split of V (n x rp); padding
-//               columns are zero.  16-bit W: L and V as hi + lo bf16 pairs (x = hi +
+//               forms L = lr U S (m x rp; tiles of 64 or 128 rows, fp32 MFMA) and, for 16-bit W, the
+//               hi/lo split of V (n x rp); padding columns are zero.  16-bit W: L and V as hi + lo bf16 pairs (x = hi +
 //               lo to about 16 significant bits, with fp32's range); fp32 W: L in
 //               fp32, V read as is.
 //   k_update_*  W <- W - L V^T in place.
@@ -53,7 +53,6 @@ constexpr int upd_cols(int rpk) { return 64 * upd_cpl(rpk); }  // columns per wo
 // 313; r = 32, d = 4096: 140 / 145 / 135; r = 16, d = 2048: 54 / 51 / 52; r = 64, d = 384: 49 / 51 / 47.
 constexpr int upd_rows(int rpk) { return rpk <= 2 ? 256 : 512; }
 constexpr int UPD_GROUP = 4;   // row chunks per raster group
-constexpr int US_ROWS = 64;    // rows of L per k_us workgroup (16 per wave)
 constexpr unsigned OOB = 0x80000000u;  // buffer offset beyond every descriptor used here
 constexpr int RSRC_CFG = 0x00020000;   // buffer descriptor word 3: 32-bit raw access
 
@@ -76,7 +75,7 @@ struct Item {
   float* wout;
   int m, n;
   int us_begin;     // first k_us workgroup of the item (over the whole call)
-  int l_tiles;      // k_us workgroups forming L (US_ROWS rows each); then V tiles (64 rows each)
+  int l_tiles;      // k_us workgroups forming L (64 or 128 rows each); then V tiles (64 rows each)
   int us_wg;        // all k_us workgroups of the item
   int up_begin;     // first update workgroup of the item
   int strips, rchunks;  // 16-bit W: strips of upd_cols columns x chunks of upd_rows rows
@@ -171,18 +170,27 @@ struct USArgs {
 
 typedef float f32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
 
-// L = lr U S for US_ROWS rows of one item, on v_mfma_f32_16x16x4_f32 (fp32 products and sums):
-// S is staged in LDS as fp32, transposed, and each wave multiplies 16 of its rows of U, read 16 bytes
+// L = lr U S for 64 NG rows of one item, on v_mfma_f32_16x16x4_f32 (fp32 products and sums):
+// S is staged in LDS as fp32, transposed, and each wave multiplies 16 NG rows of U, read 16 bytes
 // per lane straight from memory, by all of it.  A 16-byte piece feeds four MFMAs (element e of
 // every lane in MFMA e: k = 4 g + e of a 16-deep slice, the same for both operands).  S^T is
 // the A operand, so a lane ends with 4 adjacent columns of one row.  Or the hi/lo split of 64 rows of
 // V.  (On the vector FMA, 128 rows per workgroup and U staged a float at a time: 43 us for an
 // OPT-13B layer's six matrices at r = 64, against 24.)
-template <int RPK>
+//
+// r > 64: S (128 KB of float64 at r = 128, from L2) is staged half its columns at a time, so that four
+// workgroups fit a CU (the split of V streams, and shares the allocation), and in calls of many rows
+// serves 128 rows.  240 OPT-13B matrices, us, vector FMA / all of S for 64 rows / this: r = 128
+// 1790 / 2623 / 1355, r = 96 1093 / 1126 / 869.  Six matrices of d = 512 at r = 128, whole call:
+// 87 / 63 / 64 (70 with 128 rows).
+constexpr long long US_MANY = 65536;  // rows of L of a call from which NG = 2 (r > 64)
+
+template <int RPK, int NG>
 __global__ __launch_bounds__(256) void k_us(USArgs a) {
   constexpr int RP = 32 * RPK;
   constexpr int SP = RP + 4;  // pitch of S^T's rows: 16 of them at one 16-byte column on distinct banks
-  __shared__ __attribute__((aligned(16))) float St[RP * SP];
+  constexpr int SC = RPK <= 2 ? RP : RP / 2;  // columns of S staged at a time
+  __shared__ __attribute__((aligned(16))) float St[SC * SP];
   const int b = a.wg0 + (int)blockIdx.x;
   const Item it = a.it[find_item(a.begin, a.count, b)];
   const int local = b - it.us_begin;
@@ -200,53 +208,68 @@ __global__ __launch_bounds__(256) void k_us(USArgs a) {
     }
   }
   if (local < it.l_tiles) {
-    for (int x = tid; x < RP * RP; x += 256) {
-      const int t = x / RP, c = x % RP;
-      St[c * SP + t] = (t < r && c < r) ? (float)it.S[t * r + c] : 0.f;
-    }
-    __syncthreads();
     const int lane = tid & 63, l16 = lane & 15, g = lane >> 4;
-    const int row = local * US_ROWS + (tid >> 6) * 16 + l16;
-    const float* u = it.U + (size_t)min(row, it.m - 1) * r;
-    f32x4 uf[RP / 16];
+    const int row0 = local * 64 * NG + (tid >> 6) * 16 * NG + l16;
+    f32x4 uf[NG][RP / 16];
 #pragma unroll
-    for (int k = 0; k < RP / 16; ++k) {
-      const int c = 16 * k + 4 * g;
-      uf[k] = (f32x4){0.f, 0.f, 0.f, 0.f};
-      if (c + 4 <= r) {
-        uf[k] = (f32x4)*(const f32x4_a4*)(u + c);
-      } else {
-#pragma unroll
-        for (int e = 0; e < 3; ++e)
-          if (c + e < r) uf[k][e] = u[c + e];
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < RP / 16; ++j) {
-      f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+    for (int n = 0; n < NG; ++n) {
+      const float* u = it.U + (size_t)min(row0 + 16 * n, it.m - 1) * r;
 #pragma unroll
       for (int k = 0; k < RP / 16; ++k) {
-        const f32x4 sf = *(const f32x4*)&St[(16 * j + l16) * SP + 16 * k + 4 * g];
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc = __builtin_amdgcn_mfma_f32_16x16x4f32(sf[e], uf[k][e], acc, 0, 0, 0);
-      }
-      const int c = 16 * j + 4 * g;
-      float v[4], lo[4];
-#pragma unroll
-      for (int z = 0; z < 4; ++z) v[z] = a.lr * acc[z];
-      if (row < it.m) {
-        if (a.bf16) {
-          bf16_t* Lh = (bf16_t*)it.L + (size_t)row * 2 * RP + c;
-#pragma unroll
-          for (int z = 0; z < 4; ++z) lo[z] = v[z] - bf16_to_f32(f32_to_bf16(v[z]));
-          *(u32x2*)Lh = (u32x2){pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
-          *(u32x2*)(Lh + RP) = (u32x2){pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3])};
+        const int c = 16 * k + 4 * g;
+        uf[n][k] = (f32x4){0.f, 0.f, 0.f, 0.f};
+        if (c + 4 <= r) {
+          uf[n][k] = (f32x4)*(const f32x4_a4*)(u + c);
         } else {
-          // fp32 W keeps L unpadded: m x rp with rp == r.
-          float* Lf = (float*)it.L + (size_t)row * a.rp;
 #pragma unroll
-          for (int z = 0; z < 4; ++z)
-            if (c + z < a.rp) Lf[c + z] = v[z];
+          for (int e = 0; e < 3; ++e)
+            if (c + e < r) uf[n][k][e] = u[c + e];
+        }
+      }
+    }
+#pragma unroll
+    for (int c0 = 0; c0 < RP; c0 += SC) {
+      if (c0) __syncthreads();  // the previous columns have been consumed
+      for (int x = tid; x < RP * SC; x += 256) {
+        const int t = x / SC, c = x % SC;
+        St[c * SP + t] = (t < r && c0 + c < r) ? (float)it.S[t * r + c0 + c] : 0.f;
+      }
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < SC / 16; ++j) {
+        f32x4 acc[NG];
+#pragma unroll
+        for (int n = 0; n < NG; ++n) acc[n] = (f32x4){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int k = 0; k < RP / 16; ++k) {
+          const f32x4 sf = *(const f32x4*)&St[(16 * j + l16) * SP + 16 * k + 4 * g];
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int n = 0; n < NG; ++n)
+              acc[n] = __builtin_amdgcn_mfma_f32_16x16x4f32(sf[e], uf[n][k][e], acc[n], 0, 0, 0);
+        }
+        const int c = c0 + 16 * j + 4 * g;
+#pragma unroll
+        for (int n = 0; n < NG; ++n) {
+          const int row = row0 + 16 * n;
+          if (row >= it.m) continue;
+          float v[4], lo[4];
+#pragma unroll
+          for (int z = 0; z < 4; ++z) v[z] = a.lr * acc[n][z];
+          if (a.bf16) {
+            bf16_t* Lh = (bf16_t*)it.L + (size_t)row * 2 * RP + c;
+#pragma unroll
+            for (int z = 0; z < 4; ++z) lo[z] = v[z] - bf16_to_f32(f32_to_bf16(v[z]));
+            *(u32x2*)Lh = (u32x2){pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+            *(u32x2*)(Lh + RP) = (u32x2){pack_bf16x2(lo[0], lo[1]), pack_bf16x2(lo[2], lo[3])};
+          } else {
+            // fp32 W keeps L unpadded: m x rp with rp == r.
+            float* Lf = (float*)it.L + (size_t)row * a.rp;
+#pragma unroll
+            for (int z = 0; z < 4; ++z)
+              if (c + z < a.rp) Lf[c + z] = v[z];
+          }
         }
       }
     }
@@ -567,6 +590,10 @@ int zo_update_launch(int count, const zo_update_item* items, int w_dtype, int r,
   std::vector<Item> tab((size_t)count);
   long long us_total = 0, up_total = 0;
   bool hook = false;
+  long long mtotal = 0;
+  for (int k = 0; k < count; ++k) mtotal += items[k].m;
+  const bool many = r > 64 && mtotal >= US_MANY;
+  const int lrows = many ? 128 : 64;  // rows of L per k_us workgroup
   for (int k = 0; k < count; ++k) {
     const zo_update_item& src = items[k];
     const Layout lay = item_layout(src.m, src.n, r, rp, bf16, aw);
@@ -588,7 +615,7 @@ int zo_update_launch(int count, const zo_update_item* items, int w_dtype, int r,
     it.wout = src.w_f32_out;
     it.m = src.m;
     it.n = src.n;
-    it.l_tiles = (src.m + US_ROWS - 1) / US_ROWS;
+    it.l_tiles = (src.m + lrows - 1) / lrows;
     it.us_wg = it.l_tiles + (bf16 ? (src.n + 63) / 64 : 0);
     it.us_begin = (int)us_total;
     us_total += it.us_wg;
@@ -655,12 +682,14 @@ int zo_update_launch(int count, const zo_update_item* items, int w_dtype, int r,
     const long long nw = us_total - w0 < MAX_PASS_WG ? us_total - w0 : MAX_PASS_WG;
     ua.wg0 = (int)w0;
     const dim3 grid((unsigned)nw);
+#define ZO_US(RPK, NG) hipLaunchKernelGGL((k_us<RPK, NG>), grid, dim3(256), 0, stream, ua)
     switch ((rp + 31) / 32) {
-      case 1: hipLaunchKernelGGL(k_us<1>, grid, dim3(256), 0, stream, ua); break;
-      case 2: hipLaunchKernelGGL(k_us<2>, grid, dim3(256), 0, stream, ua); break;
-      case 3: hipLaunchKernelGGL(k_us<3>, grid, dim3(256), 0, stream, ua); break;
-      default: hipLaunchKernelGGL(k_us<4>, grid, dim3(256), 0, stream, ua); break;
+      case 1: ZO_US(1, 1); break;
+      case 2: ZO_US(2, 1); break;
+      case 3: if (many) { ZO_US(3, 2); } else { ZO_US(3, 1); } break;
+      default: if (many) { ZO_US(4, 2); } else { ZO_US(4, 1); } break;
     }
+#undef ZO_US
     if ((st = zo_hip_status(hipGetLastError(), "k_us")) != ZO_OK) return st;
   }
 

@@ -57,3 +57,36 @@ def test_update_tile_edges(m, n, r, off, dt):
     assert np.all(err <= bound), float(np.max(err / bound))
     stored = {"bf16": oracle.round_bf16, "f16": oracle.round_f16, "f32": lambda x: x}[dt](got.astype(np.float64))
     np.testing.assert_array_equal(host(W), stored)
+
+
+@pytest.mark.parametrize("r", [65, 96, 97, 128])
+def test_update_of_many_rows(r):
+    """Calls of many rows at r > 64 form 128 rows of L per workgroup: every item of one such call is
+    bitwise what it is alone (64 rows per workgroup), with row counts on both sides of both tiles."""
+    rng = np.random.default_rng(r)
+    sizes = [(129, 40), (64, 136), (191, 8), (65600, 8), (128, 264)]
+    assert sum(m for m, _ in sizes) >= 65536
+    q, g = 2, _off(rng.standard_normal(2), 0)
+
+    def items():
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(r)
+        f = lambda *s: torch.randn(*s, generator=gen, device="cuda")  # noqa: E731
+        return [dict(W=f(m, n).mul_(0.02).bfloat16(), U=f(m, r).mul_(0.1), V=f(n, r).mul_(0.1), Z=f(q, r, r),
+                     M1=f(r, r).mul_(0.1), M2=f(r, r).square_()) for m, n in sizes]
+
+    together, alone = items(), items()
+    step = lambda its: zo.subspace_adam_update(its, g, 4, 1e-2, 0.9, 0.95, 1e-8)  # noqa: E731
+    step(together)
+    for k, (m, n) in enumerate(sizes):
+        if m < 65536:
+            step([alone[k]])
+        else:  # its rows in two calls of fewer
+            it, h = alone[k], 32896
+            for sl in (slice(0, h), slice(h, m)):
+                part = dict(it, W=it["W"][sl].clone(), U=it["U"][sl].clone(), M1=it["M1"].clone(), M2=it["M2"].clone())
+                step([part])
+                it["W"][sl] = part["W"]
+            it["M1"], it["M2"] = part["M1"], part["M2"]
+        for name in ("W", "M1", "M2"):
+            assert torch.equal(together[k][name], alone[k][name]), (k, name)
