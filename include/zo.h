@@ -110,6 +110,8 @@ const char* zo_last_error_detail(void);
  *           column gives this).
  *           R_kk is then reported as 0, the Q column is zero and the other
  *           columns are formed as if column k were absent.
+ *           A panel with a non-finite entry is reported too, at the entry's
+ *           column or an earlier one; its Q is not to be used.
  * Limits: 1 <= r <= ZO_MAX_QR_RANK, rows <= 2^26.  Panels of one call share
  * r; rows may differ.
  * ------------------------------------------------------------------------ */

@@ -119,3 +119,16 @@ def test_outputs_that_overlap(r, sizes):
         for k in range(3):
             same(q[k], refq[k])
             same(rd[k], refd[k])
+
+
+@pytest.mark.parametrize("r", [16, 64, 100])
+@pytest.mark.parametrize("bad", [float("nan"), float("inf")])
+def test_non_finite_panel_is_reported(r, bad):
+    """At the entry's column or before it, and the call's other panels are what they are alone."""
+    rng = np.random.default_rng(r)
+    om = [dev_f32(rng.standard_normal((600, r))) for _ in range(2)]
+    alone, _, _ = run([om[1]], r, [torch.empty_like(om[1])])
+    om[0][5, r - 3] = bad
+    q, _, info = run(om, r, [torch.empty_like(o) for o in om])
+    assert 1 <= info[0] <= r - 2 and info[1] == 0
+    np.testing.assert_array_equal(q[1].view(np.uint32), alone[0].view(np.uint32))
